@@ -698,8 +698,33 @@ __device__ float block_sum(float v, float* red) {
   return t;
 }
 
+// Dot products of an LDS row with a weight row (both 16-B aligned, n a
+// multiple of 4): by one thread, or by the 16 lanes of a group (every lane gets
+// the sum).  One thread per unit left 240 of 256 idle over d dependent loads.
+__device__ __forceinline__ float dot_f32(const float* x, const float* w, int n) {
+  float s = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < n; k += 4) {
+    const float4 p = *reinterpret_cast<const float4*>(x + k), q = *reinterpret_cast<const float4*>(w + k);
+    s += (p.x * q.x + p.y * q.y) + (p.z * q.z + p.w * q.w);
+  }
+  return s;
+}
+__device__ __forceinline__ float dot16_f32(const float* x, const float* w, int n) {
+  float s = 0.f;
+#pragma unroll 4
+  for (int k = 4 * (threadIdx.x % 16); k < n; k += 64) {
+    const float4 p = *reinterpret_cast<const float4*>(x + k), q = *reinterpret_cast<const float4*>(w + k);
+    s += (p.x * q.x + p.y * q.y) + (p.z * q.z + p.w * q.w);
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  return s;
+}
+
 __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
-  extern __shared__ float sh[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float* sh = reinterpret_cast<float*>(smem);
   const int d = a.d, m = a.m, t = blockIdx.x;
   float* sz = sh;        // [d]
   float* sg = sz + d;    // [m]
@@ -713,9 +738,9 @@ __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
   for (int i = threadIdx.x; i < d; i += blockDim.x) sz[i] = z[i];
   __syncthreads();
   if (has_ad)
-    for (int j = threadIdx.x; j < m; j += blockDim.x) {
-      float u = 0.f;
-      for (int k = 0; k < d; ++k) u += sz[k] * wdt[(long)j * d + k];
+    for (int j = threadIdx.x / 16; j < m; j += 16) {
+      const float u = dot16_f32(sz, wdt + (long)j * d, d);
+      if (threadIdx.x % 16) continue;
       if (a.u) static_cast<float*>(a.u)[(long)t * m + j] = u;
       sg[j] = gelu_f(u);
     }
@@ -723,8 +748,7 @@ __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
   float s1 = 0.f;
   for (int f = threadIdx.x; f < d; f += blockDim.x) {
     float v = res[f] + sz[f];
-    if (has_ad)
-      for (int j = 0; j < m; ++j) v += sg[j] * wut[(long)f * m + j];
+    if (has_ad) v += dot_f32(sg, wut + (long)f * m, m);
     sv[f] = v;
     s1 += v;
   }
@@ -752,7 +776,8 @@ __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
 }
 
 __global__ __launch_bounds__(256) void adapter_bwd_f32(AdapterBwdArgs a) {
-  extern __shared__ float sh[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float* sh = reinterpret_cast<float*>(smem);
   const int d = a.d, m = a.m, t = blockIdx.x;
   float* sdz = sh;       // [d]
   float* sdu = sdz + d;  // [m]
@@ -787,9 +812,9 @@ __global__ __launch_bounds__(256) void adapter_bwd_f32(AdapterBwdArgs a) {
   const float* wu = static_cast<const float*>(a.wup);
   const float* wd = static_cast<const float*>(a.wdn);
   const float* u = static_cast<const float*>(a.u) + (long)t * m;
-  for (int j = threadIdx.x; j < m; j += blockDim.x) {
-    float dv = 0.f;
-    for (int f = 0; f < d; ++f) dv += sdz[f] * wu[(long)j * d + f];
+  for (int j = threadIdx.x / 16; j < m; j += 16) {
+    const float dv = dot16_f32(sdz, wu + (long)j * d, d);
+    if (threadIdx.x % 16) continue;
     const float du = dv * gelu_grad_f(u[j]);
     sdu[j] = du;
     static_cast<float*>(a.du)[(long)t * m + j] = du;
@@ -798,32 +823,60 @@ __global__ __launch_bounds__(256) void adapter_bwd_f32(AdapterBwdArgs a) {
   __syncthreads();
   float* dzin = static_cast<float*>(a.dzin) + (long)t * d;
   for (int f = threadIdx.x; f < d; f += blockDim.x) {
-    float v = sdz[f];
-    for (int j = 0; j < m; ++j) v += sdu[j] * wd[(long)f * m + j];
-    dzin[f] = v;
+    dzin[f] = sdz[f] + dot_f32(sdu, wd + (long)f * m, m);
   }
 }
 
-// one thread per gradient entry, summing over every token
-__global__ __launch_bounds__(256) void adapter_dw_f32(AdapterDwArgs a) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long n = (long)a.m * a.d;
-  if (i >= 2 * n) return;
-  const float* U = static_cast<const float*>(a.u);
-  const float* dZ = static_cast<const float*>(a.dz);
-  const float* Z = static_cast<const float*>(a.z);
-  const float* dU = static_cast<const float*>(a.du);
-  float s = 0.f;
-  if (i < n) {  // g_up[j][f]
-    const int j = (int)(i / a.d), f = (int)(i % a.d);
-    for (int t = 0; t < a.T; ++t) s += gelu_f(U[(long)t * a.m + j]) * dZ[(long)t * a.d + f];
-    a.g_up[i] += s;
-  } else {      // g_down[f][j]
-    const long k = i - n;
-    const int f = (int)(k / a.m), j = (int)(k % a.m);
-    for (int t = 0; t < a.T; ++t) s += Z[(long)t * a.d + f] * dU[(long)t * a.m + j];
-    a.g_down[k] += s;
+// Weight gradients of up to DW_BATCH adapters: 16x16 output tiles of
+// C[p][q] += sum_t X[t][p] Y[t][q] (output kinds as in adapter_dw_bf16), the
+// tokens in blocks of 16 dealt to the workgroup's eight waves, MFMA 16x16x4 f32
+// with both operands read straight from the token-major rows (lane group g
+// takes tokens 4g .. 4g+3 of a block), the waves' sums added in LDS in wave
+// order.  Rows and columns past the matrix read its last one and are not
+// stored.  128 tokens, d 128, m 16, four adapters: 4 x 51 -> 4.8 us (one
+// thread per entry, all tokens in series, one launch per adapter).
+constexpr int DWF_NW = 8;
+__global__ __launch_bounds__(64 * DWF_NW) void adapter_dw_f32(AdapterDwBatch batch) {
+  __shared__ float red[DWF_NW][16][17];
+  const int bz = blockIdx.y;
+  const AdapterDwArgs& a = batch.a[bz >> 1];
+  const bool up = (bz & 1) == 0;
+  const int nx = up ? a.m : a.d, ny = up ? a.d : a.m, T = a.T;  // C is nx x ny, X rows nx wide, Y rows ny wide
+  const int ntq = (ny + 15) / 16, p0 = blockIdx.x / ntq * 16, q0 = blockIdx.x % ntq * 16;
+  const float* X = static_cast<const float*>(up ? a.u : a.z);
+  const float* Y = static_cast<const float*>(up ? a.dz : a.du);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, grp = lane >> 4;
+  const float* xp = X + min(p0 + l16, nx - 1);
+  const float* yp = Y + min(q0 + l16, ny - 1);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int PF = 4;  // blocks in flight
+  for (int t0 = wave * 16; t0 < T; t0 += 16 * DWF_NW * PF) {
+    float x[PF][4], y[PF][4];
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int t = t0 + p * 16 * DWF_NW + 4 * grp + e;
+        const long row = min(t, T - 1);
+        x[p][e] = xp[row * nx];
+        y[p][e] = yp[row * ny];
+        if (t >= T) x[p][e] = y[p][e] = 0.f;
+      }
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(up ? gelu_f(x[p][e]) : x[p][e], y[p][e], acc, 0, 0, 0);
   }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][4 * grp + r][l16] = acc[r];
+  __syncthreads();
+  const int i = threadIdx.x / 16, j = threadIdx.x % 16;
+  if (i >= 16 || p0 + i >= nx || q0 + j >= ny) return;
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < DWF_NW; ++w) s += red[w][i][j];
+  (up ? a.g_up : a.g_down)[(long)(p0 + i) * ny + q0 + j] += s;
 }
 
 // ================================================================ launchers
@@ -1000,9 +1053,14 @@ hipError_t launch_adapter_dw_batch(int dtype, const AdapterDwArgs* a, int n, flo
   }
   if (n == 0 || a[0].T == 0) return hipSuccess;
   if (dtype != DT_BF16) {
-    for (int k = 0; k < n; ++k) {
-      const long ne = 2L * a[k].m * a[k].d;
-      RG_LAUNCH(adapter_dw_f32, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, s, a[k]);
+    for (int k = 1; k < n; ++k)
+      if (a[k].T != a[0].T || a[k].d != a[0].d || a[k].m != a[0].m) return hipErrorInvalidValue;
+    for (int k0 = 0; k0 < n; k0 += DW_BATCH) {
+      const int nb = n - k0 < DW_BATCH ? n - k0 : DW_BATCH;
+      AdapterDwBatch b{};
+      for (int k = 0; k < nb; ++k) b.a[k] = a[k0 + k];
+      RG_LAUNCH(adapter_dw_f32, dim3((unsigned)((a[0].m + 15) / 16 * ((a[0].d + 15) / 16)), 2 * nb),
+                dim3(64 * DWF_NW), 0, s, b);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

@@ -10,7 +10,7 @@
 // FFN width of 64; 16-B aligned operands); others are refused.  The MFMA
 // computes C^T blocks so that each lane owns four consecutive output columns
 // of one row.
-// f32: a plain FMA tile kernel (used by the small fp32 stage only).
+// f32: MFMA 16x16x4 f32 on small tiles (the small fp32 stages only).
 #include <type_traits>
 
 #include <utility>
@@ -23,29 +23,19 @@ namespace rg {
 
 // ---------------------------------------------------------------- epilogues
 // fp32 epilogue on four consecutive output columns n..n+3 of row m (the fp32
-// path is the post-LN block only: store + bias, GELU, residual, GELU')
+// path is the post-LN block only: store + bias, GELU, residual, GELU').  x: the
+// bias of those columns (Store, Gelu; zero without one) or their second operand
 template <Epi E>
-__device__ __forceinline__ void epilogue4_f32(const GemmArgs& a, int m, int n, float v[4]) {
+__device__ __forceinline__ void epilogue4_f32(const GemmArgs& a, int m, int n, float v[4], const float x[4]) {
   static_assert(E == Epi::Store || E == Epi::Gelu || E == Epi::Resid || E == Epi::DGelu,
                 "post-LN epilogues only");
   const long r = m;
-  if constexpr (E == Epi::Store || E == Epi::Gelu) {
-    if (a.bias) {
-      float b[4];
-      St<float>::ld4(static_cast<const float*>(a.bias), n, b);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] += b[i];
-    }
-    if constexpr (E == Epi::Gelu) {
-      if (a.out2) St<float>::st4(static_cast<float*>(a.out2), r * a.ldo2 + n, v);
+  for (int i = 0; i < 4; ++i) v[i] = E == Epi::DGelu ? v[i] * gelu_grad_f(x[i]) : v[i] + x[i];
+  if constexpr (E == Epi::Gelu) {
+    if (a.out2) St<float>::st4(static_cast<float*>(a.out2), r * a.ldo2 + n, v);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
-    }
-  } else {
-    float x[4];
-    St<float>::ld4(static_cast<const float*>(a.aux), r * a.ld_aux + n, x);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = E == Epi::Resid ? v[i] + x[i] : v[i] * gelu_grad_f(x[i]);
+    for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
   }
   St<float>::st4(static_cast<float*>(a.out), r * a.ldo + n, v);
 }
@@ -520,42 +510,113 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
   }
 }
 
-// ---------------------------------------------------------------- fp32 FMA kernel
-template <Epi E>
+// ---------------------------------------------------------------- fp32 kernel
+// The fp32 stages are small (a few hundred tokens, d a few hundred), so what
+// counts is the latency of one short chain on many CUs, not the arithmetic.
+// Each workgroup makes a 16R x 16R tile, its four waves taking every fourth
+// 16-wide block of K; operand fragments go from global memory straight to
+// registers, PF blocks in flight, and into MFMA 16x16x4 f32 (fp32 products and
+// sums), the weight as the A operand so that a lane ends up with four
+// consecutive output columns; the waves' sums are added in LDS in wave order.
+// The k order inside a 16-wide block is permuted the same way for both
+// operands: lane group g loads k = 4g .. 4g+3 as one 16-B piece and feeds
+// element j to the j-th MFMA.
+// 128 x 128 x 512: 58 -> 4.7 us, 2048 x 4096 x 1024: 282 -> 234 us (before: FMA on
+// 64x64 tiles, K in series through LDS).
+template <Epi E, int R>
 __device__ __forceinline__ void gemm_f32_body(const GemmArgs& a) {
-  constexpr int TB = 64, KB = 16;
-  __shared__ float sA[KB][TB + 4], sB[KB][TB + 4];
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.y * TB, n0 = blockIdx.x * TB;
+  constexpr int TB = 16 * R, KW = 4, PF = R == 1 ? 8 : 4;
+  __shared__ __attribute__((aligned(16))) float red[KW][TB][TB + 4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, grp = lane >> 4;
+  const int ntn = (a.N + TB - 1) / TB, m0 = (int)(blockIdx.x / ntn) * TB, n0 = (int)(blockIdx.x % ntn) * TB;
   const float* A = static_cast<const float*>(a.A);
   const float* B = static_cast<const float*>(a.B);
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < a.K; k0 += KB) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int idx = tid + i * 256, r = idx / KB, k = idx % KB;
-      int gk = k0 + k;
-      sA[k][r] = (m0 + r < a.M && gk < a.K) ? A[(long)(m0 + r) * a.lda + gk] : 0.f;
-      sB[k][r] = (n0 + r < a.N && gk < a.K) ? B[(long)(n0 + r) * a.ldb + gk] : 0.f;
+  // this thread's four outputs, and the bias or second operand they need
+  const int em = m0 + tid / (TB / 4), en = n0 + tid % (TB / 4) * 4;
+  const bool ev = tid < TB * TB / 4 && em < a.M && en < a.N;
+  float x[4] = {0.f, 0.f, 0.f, 0.f};
+  if (ev) {
+    if constexpr (E == Epi::Store || E == Epi::Gelu) {
+      if (a.bias) St<float>::ld4(static_cast<const float*>(a.bias), en, x);
+    } else {
+      St<float>::ld4(static_cast<const float*>(a.aux), (long)em * a.ld_aux + en, x);
     }
-    __syncthreads();
+  }
+  // rows past the end read the last one; their results are not stored
+  const float* ar[R];
+  const float* br[R];
 #pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      float x[4], y[4];
+  for (int i = 0; i < R; ++i) {
+    ar[i] = A + (long)min(m0 + 16 * i + l16, a.M - 1) * a.lda;
+    br[i] = B + (long)min(n0 + 16 * i + l16, a.N - 1) * a.ldb;
+  }
+  f32x4 acc[R][R];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { x[i] = sA[k][ty * 4 + i]; y[i] = sB[k][tx * 4 + i]; }
+  for (int i = 0; i < R; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < R; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // one loop per access width, so that no load sits in a branch of its own
+  auto loop = [&](auto VEC) {
+    auto load = [&](int k0, float (&fa)[PF][R][4], float (&fb)[PF][R][4]) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(x[i], y[j], acc[i][j]);
+      for (int p = 0; p < PF; ++p)
+#pragma unroll
+        for (int i = 0; i < 2 * R; ++i) {
+          const int k = k0 + 16 * KW * p + 4 * grp;
+          const float* src = (i < R ? ar[i] : br[i - R]) + (k < a.K ? k : 0);  // past K: masked in mul
+          float* v = i < R ? fa[p][i] : fb[p][i - R];
+          if constexpr (decltype(VEC)::value) {
+            const float4 q = *reinterpret_cast<const float4*>(src);
+            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = src[e];
+          }
+        }
+      __builtin_amdgcn_sched_barrier(0);  // keeps the scheduler from moving loads down to their MFMAs
+    };
+    auto mul = [&](int k0, const float (&fa)[PF][R][4], const float (&fb)[PF][R][4]) {
+#pragma unroll
+      for (int p = 0; p < PF; ++p) {
+        const bool in = k0 + 16 * KW * p + 4 * grp < a.K;  // K is a multiple of 4: pieces are whole or absent
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? fb[p][j][e] : 0.f, in ? fa[p][i][e] : 0.f,
+                                                               acc[i][j], 0, 0, 0);
+      }
+    };
+    constexpr int KB = 16 * KW * PF;
+    float fa[PF][R][4], fb[PF][R][4];
+    for (int k0 = wave * 16; k0 < a.K; k0 += KB) {
+      load(k0, fa, fb);
+      mul(k0, fa, fb);
     }
-    __syncthreads();
-  }
+  };
+  if ((((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15u) |
+       ((unsigned)(a.lda | a.ldb) & 3u)) == 0)
+    loop(std::true_type{});
+  else
+    loop(std::false_type{});
+  // D[n = 4 grp + r][m = l16]
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i, n = n0 + tx * 4;
-    if (m < a.M && n < a.N) epilogue4_f32<E>(a, m, n, acc[i]);
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      *reinterpret_cast<float4*>(&red[wave][16 * i + l16][16 * j + 4 * grp]) =
+          make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+  __syncthreads();
+  if (!ev) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < KW; ++w) {
+    const float4 q = *reinterpret_cast<const float4*>(&red[w][tid / (TB / 4)][tid % (TB / 4) * 4]);
+    v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
   }
+  epilogue4_f32<E>(a, em, en, v, x);
 }
 
 // ---------------------------------------------------------------- named kernels
@@ -570,9 +631,9 @@ __device__ __forceinline__ void gemm_f32_body(const GemmArgs& a) {
   __global__ __launch_bounds__(512) void NAME##_pipe8(GemmArgs a) {                  \
     gemm_bf16_pipe_body<BM, BN, WM, WN, 64, NS, E, 4>(a);                            \
   }                                                                                  \
-  template <Epi E>                                                                   \
+  template <Epi E, int R>                                                            \
   __global__ __launch_bounds__(256) void NAME##_f32(GemmArgs a) {                    \
-    gemm_f32_body<E>(a);                                                             \
+    gemm_f32_body<E, R>(a);                                                          \
   }
 
 RG_GEMM_KERNELS(gemm_qkv_fwd)
@@ -655,9 +716,18 @@ static hipError_t launch_role(Cfg cfg, int dtype, const GemmArgs& a, hipStream_t
     if (dtype == DT_F32) {
       if constexpr (!f32_has(R, E)) return hipErrorInvalidValue;
       else {
-        dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);
+        // 16-wide tiles put a small product on the most CUs, 32-wide ones read half the
+        // operand bytes: 5.7 and 5.7 us at 64 tiles of 32 (K 128), 6.9 and 5.9 at 128
+        // (K 256), 10.8 and 12.6 at 128 (K 1024), 33 and 21 at 256 (K 2048)
+        auto tiles = [&](int tb) { return (long)((a.N + tb - 1) / tb) * ((a.M + tb - 1) / tb); };
+        const bool wide = tiles(32) >= 128;
+        const dim3 grid((unsigned)tiles(wide ? 32 : 16));
         // one kernel per role, chosen at compile time (only R's kernel is instantiated)
-#define RG_F32(ROLE, NAME) if constexpr (R == ROLE) RG_LAUNCH((NAME##_f32<E>), grid, block, 0, s, a); else
+#define RG_F32(ROLE, NAME)                                             \
+  if constexpr (R == ROLE) {                                           \
+    if (wide) RG_LAUNCH((NAME##_f32<E, 2>), grid, block, 0, s, a);     \
+    else RG_LAUNCH((NAME##_f32<E, 1>), grid, block, 0, s, a);          \
+  } else
         RG_F32(R_QKV_FWD, gemm_qkv_fwd) RG_F32(R_O_FWD, gemm_o_fwd) RG_F32(R_FFN_IN_FWD, gemm_ffn_in_fwd)
         RG_F32(R_FFN_OUT_FWD, gemm_ffn_out_fwd) RG_F32(R_QKV_DX, gemm_qkv_dx) RG_F32(R_O_DX, gemm_o_dx)
         RG_F32(R_FFN_IN_DX, gemm_ffn_in_dx) RG_F32(R_FFN_OUT_DX, gemm_ffn_out_dx)
@@ -776,7 +846,7 @@ hipError_t launch_gemm(int dtype, Role role, Epi epi, const GemmArgs& a_in, hipS
     else if (a.K > 1024 && a.N % 128 == 0 && tiles(256, 128) >= 256) cfg = C_P256x128_8W;
     else cfg = c128;
   } else if (dtype == DT_F32) {
-    if (!al16(a.out)) return hipErrorInvalidValue;
+    if (!al16(a.out) || a.K % 4) return hipErrorInvalidValue;
   } else {
     return hipErrorInvalidValue;
   }
