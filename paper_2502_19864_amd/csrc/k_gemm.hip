@@ -191,11 +191,14 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
   constexpr int CPF = BN + 4;
   constexpr bool HAS_BIAS = E == Epi::Store || E == Epi::Gelu || E == Epi::Attn;
   constexpr int BIASB = HAS_BIAS ? BN * 4 : 0;
-  constexpr int RPP = epi_rows(BM, CPF * 4, NS * STAGE - BIASB);
-  static_assert(RPP >= 32 && BM % RPP == 0 && RPP * CPF * 4 + BIASB <= NS * STAGE,
+  // (256x256 blocks take 3 KB more than their stages: two passes instead of four)
+  constexpr int EPI_LDS = BM == 256 && BN == 256 ? 128 * CPF * 4 + BIASB : NS * STAGE;
+  constexpr int RPP = epi_rows(BM, CPF * 4, EPI_LDS - BIASB);
+  static_assert(RPP >= 32 && BM % RPP == 0 && RPP * CPF * 4 + BIASB <= EPI_LDS,
                 "epilogue passes of whole 32-row blocks");
+  constexpr int LDS = EPI_LDS > NS * STAGE ? EPI_LDS : NS * STAGE;
   // the DMA is invisible to the compiler, so one array serves every stage
-  __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
+  __shared__ __attribute__((aligned(1024))) char smem[LDS];
   auto stage_base = [&](auto S) -> char* { return smem + decltype(S)::value * STAGE; };
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -250,14 +253,16 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
     const int r = (i * NW + wave) * RPI + lrow;
     ob[i] = (uint32_t)(((long)min(n0 + r, N - 1) * a.ldb + (lpos ^ ((r / SWD) % CPR)) * 8) * 2);
   }
-  auto issue = [&](int kt, char* sb) {
+  // part p of `of` equal parts of k-tile kt's DMA instructions
+  auto issue = [&](int kt, char* sb, int p, int of) {
     const char* gA = reinterpret_cast<const char*>(A) + (long)kt * BK * 2;
     const char* gB = reinterpret_cast<const char*>(B) + (long)kt * BK * 2;
     const uint32_t l0 = lds_addr(sb);
 #pragma unroll
-    for (int i = 0; i < LA; ++i) dma16_m0(gA, oa[i], l0 + (i * NW + wave_u) * RPI * ROWB);
-#pragma unroll
-    for (int i = 0; i < LB; ++i) dma16_m0(gB, ob[i], l0 + (BM + (i * NW + wave_u) * RPI) * ROWB);
+    for (int i = LPT * p / of; i < LPT * (p + 1) / of; ++i) {
+      if (i < LA) dma16_m0(gA, oa[i], l0 + (i * NW + wave_u) * RPI * ROWB);
+      else dma16_m0(gB, ob[i - LA], l0 + (BM + ((i - LA) * NW + wave_u) * RPI) * ROWB);
+    }
   };
 
   f32x16 acc[FM][FN];
@@ -300,14 +305,24 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
   };
 
   // prologue: tiles 0..NS-1 in flight, tile 0 landed, its first fragments read
-  issue(0, smem);
-  if (1 < nk) issue(1, smem + STAGE);
-  if constexpr (NS > 2) if (2 < nk) issue(2, smem + 2 * STAGE);
-  if constexpr (NS > 3) if (3 < nk) issue(3, smem + 3 * STAGE);
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    if (t < nk) issue(t, smem + t * STAGE, 0, 1);
   wait_tiles(min(NS, nk) - 1);
   barrier();
   read_frags(smem, 0, 0);
 
+  // A finished stage's refill is issued in PARTS pieces, the first right after the
+  // barrier that frees the stage, the others in the k-steps after it: issued all
+  // at once, the waves' DMA instructions (64 KB per k-tile of a 256x256 block) queue
+  // up in the address unit and hold back the MFMAs behind them.  The last piece
+  // goes out before the wait of the next k-tile, so the vmcnt bookkeeping is
+  // that of whole tiles.  With two stages the refill has only that one k-tile to
+  // arrive in, so it is cut in two only.  One piece -> PARTS, in us: 256x128
+  // 160 -> 152 (2048 x 4096 x 11008), 128x96 23.8 -> 21.4 (4096 x 768 x 3072),
+  // 128x128 35.8 -> 33.0 (4096 x 1024 x 4096), two stages: 128x192 22.2 -> 21.1
+  // (4096 x 3072 x 768).
+  constexpr int PARTS = NS >= 3 ? KS : 2;
   auto step = [&](auto S, int kt) {
     constexpr int s_ = decltype(S)::value;
     constexpr int sn = (s_ + 1) % NS;
@@ -315,12 +330,14 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       if (ks + 1 < KS) {
+        if (ks + 1 < PARTS && kt > 0 && kt - 1 + NS < nk)
+          issue(kt - 1 + NS, stage_base(std::integral_constant<int, (s_ + NS - 1) % NS>{}), ks + 1, PARTS);
         read_frags(base, ks + 1, (ks + 1) & 1);
       } else if (kt + 1 < nk) {
         // tile kt+1: tiles issued after it are kt+2 .. min(kt+NS-1, nk-1)
         wait_tiles(min(NS - 2, nk - 2 - kt));
         barrier();
-        if (kt + NS < nk) issue(kt + NS, stage_base(S));
+        if (kt + NS < nk) issue(kt + NS, stage_base(S), 0, PARTS);
         read_frags(stage_base(std::integral_constant<int, sn>{}), 0, 0);
       }
       mfmas(ks & 1);
@@ -345,7 +362,7 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
   }
   barrier();  // every wave is done reading operand tiles
   float* cf = reinterpret_cast<float*>(smem);
-  float* cbias = reinterpret_cast<float*>(smem + NS * STAGE - BIASB);
+  float* cbias = reinterpret_cast<float*>(smem + LDS - BIASB);
   if constexpr (HAS_BIAS)
     if (a.bias && tid < BN / 8) {
       float f[8];
@@ -451,8 +468,8 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
       }
     } else if constexpr (E == Epi::Rope) {
       // chunk pairs: 8 columns at head-local offset i < dh/2 and the 8 at
-      // i + dh/2; the tile spans whole heads (BN = 128, n0 a multiple of 128)
-      static_assert(BN == 128, "rotary epilogue on 128-wide tiles only");
+      // i + dh/2; the tile spans whole heads (BN and n0 multiples of 128)
+      static_assert(BN % 128 == 0, "rotary epilogue on whole heads only");
       constexpr int NPAIR = RPP * CPRW8 / 2;
       static_assert(NPAIR % NT == 0, "whole passes");
       const int dh = a.rope_dh, hc = dh / 16;  // pairs of chunks per head
