@@ -640,13 +640,10 @@ __device__ __forceinline__ void gemm_f32_body(const GemmArgs& a) {
 // Two-stage 4-wave tiles run two workgroups per CU (LDS <= 80 KB), so their
 // registers must fit two waves per SIMD; the bound says so to the compiler.
 #define RG_GEMM_KERNELS(NAME)                                                        \
-  template <int BM, int BN, int WM, int WN, int NS, Epi E>                           \
-  __global__ __launch_bounds__(256, NS == 2 ? 2 : 1) void NAME##_pipe(GemmArgs a) {  \
-    gemm_bf16_pipe_body<BM, BN, WM, WN, 64, NS, E, 4>(a);                            \
-  }                                                                                  \
-  template <int BM, int BN, int WM, int WN, int NS, Epi E>                           \
-  __global__ __launch_bounds__(512) void NAME##_pipe8(GemmArgs a) {                  \
-    gemm_bf16_pipe_body<BM, BN, WM, WN, 64, NS, E, 4>(a);                            \
+  template <int BM, int BN, int WM, int WN, int BK, int NS, Epi E>                   \
+  __global__ __launch_bounds__(64 * WM * WN, NS == 2 && WM * WN == 4 ? 2 : 1) void   \
+  NAME##_pipe(GemmArgs a) {                                                          \
+    gemm_bf16_pipe_body<BM, BN, WM, WN, BK, NS, E, 4>(a);                            \
   }                                                                                  \
   template <Epi E, int R>                                                            \
   __global__ __launch_bounds__(256) void NAME##_f32(GemmArgs a) {                    \
@@ -680,38 +677,58 @@ static constexpr bool role_has(Role r, Epi e) {
   }
 }
 
-// Tile shapes of the pipelined kernel (BK = 64), chosen per GEMM shape by
-// measurement on the BERT-base, BERT-large and LLaMA-7B stage shapes:
-//  - 128x192 (2x2 waves of 64x96, two stages) for wide outputs with K <= 1024;
-//  - 128x96 (4x1 waves of 32x96, three stages) for outputs up to 1024 wide
-//    that 96 divides;
-//  - for K > 1024, 256x192 (8 waves of 64x96, two stages) or 256x128 (8
-//    waves of 64x64, three stages: one workgroup per CU either way, and the
-//    third stage hides the HBM latency of weights that no cache holds, 10-17%
-//    on the LLaMA-7B shapes) when that still gives every CU a tile;
-//  - 128x128 (2x2 waves of 64x64) otherwise: two stages (two workgroups per
-//    CU) from two tiles per CU on, three stages below.
-// The SwiGLU epilogues take only the 64-wide wave tiles (a gate/up block pair
-// per wave): 256x128 or 128x128.
-enum Cfg { C_P128x192, C_P128x96, C_P128x128_2, C_P128x128_3, C_P256x192_8W, C_P256x128_8W };
+// Tile shapes of the pipelined kernel.  A launch takes as long as its rounds of
+// workgroups, and a round costs about f + r K / 64 us (f: launch, first loads,
+// epilogue), so the tile with the least sum over its rounds is taken.  The
+// figures are fitted to launches whose operands come from memory, as they do
+// inside a stage; each shape wins somewhere, in us (against the next best here):
+//   256x256  4096 x 4096 x 1024   34.6 (256x128 39.8)
+//   256x192  4096 x 3072 x 1024   28.8 (128x192 29.1)
+//   256x128  2048 x 4096 x 11008   155 (128x128 205)
+//   128x192  4096 x 3072 x 768    22.2 (256x192 23.7); four stages for one
+//            tile per CU: 1827 x 3072 x 768 13.5 (256x128 14.7)
+//   128x128  4096 x 1024 x 4096   39.0 (128x192 45.1); two stages for two per CU:
+//            4096 x 5120 x 256, where 256-row tiles leave their last round short
+//   128x96   4096 x 768 x 3072    27.6 (128x128 31.6)
+//   64x128   1827 x 768 x 3072    20.8 (128x96 26.2)
+//   64x64    256 x 4096 x 4096    20.4 (64x128 27.2)
+//   64x32    100 x 4096 x 11008   38.6 (64x64 46.5)
+// slots: workgroups the chip holds.  Where that is 512 (two per CU), (f, r) are those of
+// a full round and (f1, r1) those of one with at most a workgroup per CU.
+enum Cfg {
+  C_64x32, C_64x64, C_64x128, C_64x128_K64, C_128x96, C_128x128, C_128x128_2, C_128x192, C_128x192_2,
+  C_256x128, C_256x192, C_256x256, N_CFGS
+};
+struct Tile { int bm, bn, bk, slots; float f, r, f1, r1; };
+static constexpr Tile TILE[N_CFGS] = {
+    {64, 32, 128, 256, 2.0f, .21f, 0, 0},      {64, 64, 128, 256, 2.5f, .27f, 0, 0},
+    {64, 128, 128, 256, 2.2f, .40f, 0, 0},     {64, 128, 64, 256, 2.3f, .43f, 0, 0},
+    {128, 96, 64, 256, 3.9f, .49f, 0, 0},      {128, 128, 64, 256, 3.3f, .56f, 0, 0},
+    {128, 128, 64, 512, 4.5f, .96f, 3.0f, .8f}, {128, 192, 64, 256, 4.6f, .73f, 0, 0},
+    {128, 192, 64, 512, 4.6f, 1.47f, 3.9f, .97f}, {256, 128, 64, 256, 3.5f, .89f, 0, 0},
+    {256, 192, 64, 256, 8.5f, 1.27f, 0, 0},    {256, 256, 64, 256, 9.0f, 1.6f, 0, 0}};
 
-// The (role, epilogue, tile) kernels that launch_gemm can select for a stage,
-// the only ones instantiated.  Besides what role_has excludes:
-//  - the gated and rotary epilogues take only the 64-wide wave tiles;
-//  - the QKV-dX GEMM has K = 3N, so N divisible by 192 (N = d a multiple of
-//    256) means K > 1024, past the 128x192 tile's K limit;
-//  - the QKV projection's output (N = 3d) is a multiple of 192, so it takes
-//    128x192 (K <= 1024) or an 8-wave tile (K > 1024) whenever the tiles
-//    would fill two workgroups per CU on 128x128; its 128x128 tiles are the
-//    three-stage ones.
-static constexpr bool cfg_has(Role R, Epi E, Cfg c) {
-  const bool glu = E == Epi::SwiGlu || E == Epi::DSwiGlu || E == Epi::Rope;
+// Tiles an epilogue can take: SwiGLU needs gate/up block pairs (64 columns) in
+// a wave, the rotary epilogue whole heads (128 columns) in a tile.
+static constexpr bool cfg_has(Epi E, Cfg c) {
   switch (c) {
-    case C_P128x192: return !glu && R != R_QKV_DX;
-    case C_P128x96: case C_P256x192_8W: return !glu;
-    case C_P128x128_2: return !(R == R_QKV_FWD && E == Epi::Store);
-    default: return true;
+    case C_64x128: case C_64x128_K64: case C_128x128: case C_128x128_2: case C_256x128: case C_256x256: return true;
+    default: return E != Epi::SwiGlu && E != Epi::Rope;
   }
+}
+
+static Cfg choose_tile(Epi E, int M, int N, int K) {
+  Cfg best = C_64x128_K64;
+  double least = 1e30;
+  for (int c = 0; c < N_CFGS; ++c) {
+    const Tile& t = TILE[c];
+    if (!cfg_has(E, (Cfg)c) || K % t.bk) continue;
+    const long n = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), full = n / t.slots, rem = n % t.slots;
+    const double k = K / 64, round = t.f + t.r * k;
+    const double us = full * round + (rem == 0 ? 0. : (t.slots > 256 && rem <= 256) ? t.f1 + t.r1 * k : round);
+    if (us < least) { least = us; best = (Cfg)c; }
+  }
+  return best;
 }
 // fp32 stages are post-LN only: no gated or rotary epilogue, and the dX
 // GEMMs of the QKV and FFN-in projections add the residual
@@ -727,7 +744,7 @@ static hipError_t launch_role(Cfg cfg, int dtype, const GemmArgs& a, hipStream_t
   } else {
     const dim3 block(256);
     if constexpr (E == Epi::Attn) {  // bf16, 128x192 tiles only (checked by the caller)
-      RG_LAUNCH((gemm_qkv_fwd_pipe<128, 192, 2, 2, 2, Epi::Attn>), dim3((a.N / 192) * (a.M / 128)), block, 0, s, a);
+      RG_LAUNCH((gemm_qkv_fwd_pipe<128, 192, 2, 2, 64, 2, Epi::Attn>), dim3((a.N / 192) * (a.M / 128)), block, 0, s, a);
       return hipGetLastError();
     } else {
     if (dtype == DT_F32) {
@@ -753,21 +770,29 @@ static hipError_t launch_role(Cfg cfg, int dtype, const GemmArgs& a, hipStream_t
         return hipGetLastError();
       }
     }
-#define RG_TILES(BM, BN) dim3(((a.N + BN - 1) / BN) * ((a.M + BM - 1) / BM))
-#define RG_CASE(C, K, BM_, BN_, THREADS)                                                    \
-    case C:                                                                                \
-      if constexpr (cfg_has(R, E, C)) RG_LAUNCH((K), RG_TILES(BM_, BN_), dim3(THREADS), 0, s, a); \
-      else return hipErrorInvalidValue;                                                    \
+#define RG_CASE(C, NAME, WM, WN, NS)                                                          \
+    case C:                                                                                  \
+      if constexpr (cfg_has(E, C))                                                           \
+        RG_LAUNCH((NAME##_pipe<TILE[C].bm, TILE[C].bn, WM, WN, TILE[C].bk, NS, E>),          \
+                  dim3(((a.N + TILE[C].bn - 1) / TILE[C].bn) * ((a.M + TILE[C].bm - 1) / TILE[C].bm)), \
+                  dim3(64 * WM * WN), 0, s, a);                                              \
+      else return hipErrorInvalidValue;                                                      \
       break;
-#define RG_LAUNCH_CFG(NAME)                                                               \
-  switch (cfg) {                                                                          \
-    RG_CASE(C_P128x192, (NAME##_pipe<128, 192, 2, 2, 2, E>), 128, 192, 256)               \
-    RG_CASE(C_P128x96, (NAME##_pipe<128, 96, 4, 1, 3, E>), 128, 96, 256)                  \
-    RG_CASE(C_P128x128_2, (NAME##_pipe<128, 128, 2, 2, 2, E>), 128, 128, 256)             \
-    RG_CASE(C_P128x128_3, (NAME##_pipe<128, 128, 2, 2, 3, E>), 128, 128, 256)             \
-    RG_CASE(C_P256x192_8W, (NAME##_pipe8<256, 192, 4, 2, 2, E>), 256, 192, 512)           \
-    RG_CASE(C_P256x128_8W, (NAME##_pipe8<256, 128, 4, 2, 3, E>), 256, 128, 512)           \
-    default: return hipErrorInvalidValue;                                                 \
+#define RG_LAUNCH_CFG(NAME)                      \
+  switch (cfg) {                                 \
+    RG_CASE(C_64x32, NAME, 2, 1, 4)              \
+    RG_CASE(C_64x64, NAME, 2, 2, 3)              \
+    RG_CASE(C_64x128, NAME, 2, 2, 3)             \
+    RG_CASE(C_64x128_K64, NAME, 2, 2, 4)         \
+    RG_CASE(C_128x96, NAME, 4, 1, 4)             \
+    RG_CASE(C_128x128, NAME, 2, 2, 3)            \
+    RG_CASE(C_128x128_2, NAME, 2, 2, 2)          \
+    RG_CASE(C_128x192, NAME, 2, 2, 4)            \
+    RG_CASE(C_128x192_2, NAME, 2, 2, 2)          \
+    RG_CASE(C_256x128, NAME, 4, 2, 3)            \
+    RG_CASE(C_256x192, NAME, 4, 2, 2)            \
+    RG_CASE(C_256x256, NAME, 4, 2, 2)            \
+    default: return hipErrorInvalidValue;        \
   }
     // only R's kernels are instantiated
     if constexpr (R == R_QKV_FWD) { RG_LAUNCH_CFG(gemm_qkv_fwd) }
@@ -781,7 +806,6 @@ static hipError_t launch_role(Cfg cfg, int dtype, const GemmArgs& a, hipStream_t
     else return hipErrorInvalidValue;
 #undef RG_LAUNCH_CFG
 #undef RG_CASE
-#undef RG_TILES
     return hipGetLastError();
     }
   }
@@ -820,11 +844,11 @@ hipError_t launch_gemm(int dtype, Role role, Epi epi, const GemmArgs& a_in, hipS
                     al16(a.out2) && (!a.bias || al16(a.bias)) && (!a.out || (a.ldo % 8 == 0 && al16(a.out))) &&
                     ((double)(a.M - 1) * a.lda + a.K) * 2 < 4294967296.0 &&
                     ((double)(a.N - 1) * a.ldb + a.K) * 2 < 4294967296.0;
-    return ok ? launch_epi<R_QKV_FWD>(epi, C_P128x192, dtype, a, s) : hipErrorInvalidValue;
+    return ok ? launch_epi<R_QKV_FWD>(epi, C_128x192_2, dtype, a, s) : hipErrorInvalidValue;
   }
   if (a.M < 0 || a.N <= 0 || a.K <= 0 || !a.A || !a.B || !a.out) return hipErrorInvalidValue;
-  // rotary epilogue: bf16 QKV projection without bias, 128-wide tiles holding
-  // whole heads of 64 or 128 columns, the pipelined kernel only (below)
+  // rotary epilogue: bf16 QKV projection without bias, tiles holding whole heads
+  // of 64 or 128 columns, the pipelined kernel only (below)
   const bool rope = epi == Epi::Rope;
   if (rope && (dtype != DT_BF16 || role != R_QKV_FWD || a.bias || !a.rope_tab || a.rope_S <= 0 ||
                (a.rope_dh != 64 && a.rope_dh != 128) || a.rope_cols % a.rope_dh || a.rope_cols > a.N ||
@@ -836,7 +860,7 @@ hipError_t launch_gemm(int dtype, Role role, Epi epi, const GemmArgs& a_in, hipS
     return hipErrorInvalidValue;
   if ((epi == Epi::SwiGlu || epi == Epi::DSwiGlu) && (a.half % 4)) return hipErrorInvalidValue;
   if (a.out2 && a.ldo2 % 4) return hipErrorInvalidValue;
-  Cfg cfg = C_P128x128_3;  // (the fp32 kernel has one tile shape)
+  Cfg cfg = C_128x128;  // (the fp32 kernel has tiles of its own)
   if (dtype == DT_BF16) {
     // 16-B operand chunks and 8-B epilogue vectors
     if (a.K % 8 || a.lda % 8 || a.ldb % 8 || !al16(a.A) || !al16(a.B) || !al8(a.out))
@@ -849,68 +873,26 @@ hipError_t launch_gemm(int dtype, Role role, Epi epi, const GemmArgs& a_in, hipS
                         (!a.out2 || (al16(a.out2) && a.ldo2 % 8 == 0)) && a.half % 8 == 0;
     const bool small_off = ((double)(a.M - 1) * a.lda + a.K) * 2 < 4294967296.0 &&
                            ((double)(a.N - 1) * a.ldb + a.K) * 2 < 4294967296.0;
-    auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    // two stages (two workgroups per CU) once there are two 128x128 tiles per CU
-    const Cfg c128 = tiles(128, 128) >= 512 ? C_P128x128_2 : C_P128x128_3;
     // (a bf16 stage always meets these: d a multiple of 256, the FFN width of
     // 64, 16-B aligned buffers, tensors under 2^31 elements)
     if (a.K % 64 || !al_epi || !small_off) return hipErrorInvalidValue;
-    // the gated and rotary epilogues take only the 64-wide wave tiles
-    const bool glu = epi == Epi::SwiGlu || epi == Epi::DSwiGlu || rope;
-    if (!glu && a.N % 192 == 0 && a.K <= 1024 && tiles(128, 192) >= 256) cfg = C_P128x192;
-    else if (!glu && a.N % 96 == 0 && a.N <= 1024) cfg = C_P128x96;
-    else if (!glu && a.K > 1024 && a.N % 192 == 0 && tiles(256, 192) >= 256) cfg = C_P256x192_8W;
-    else if (a.K > 1024 && a.N % 128 == 0 && tiles(256, 128) >= 256) cfg = C_P256x128_8W;
-    else cfg = c128;
+    cfg = choose_tile(epi, a.M, a.N, a.K);
   } else if (dtype == DT_F32) {
     if (!al16(a.out) || a.K % 4) return hipErrorInvalidValue;
   } else {
     return hipErrorInvalidValue;
   }
-  auto go = [&](Cfg c, const GemmArgs& g) -> hipError_t {
-    switch (role) {
-      case R_QKV_FWD: return launch_epi<R_QKV_FWD>(epi, c, dtype, g, s);
-      case R_O_FWD: return launch_epi<R_O_FWD>(epi, c, dtype, g, s);
-      case R_FFN_IN_FWD: return launch_epi<R_FFN_IN_FWD>(epi, c, dtype, g, s);
-      case R_FFN_OUT_FWD: return launch_epi<R_FFN_OUT_FWD>(epi, c, dtype, g, s);
-      case R_QKV_DX: return launch_epi<R_QKV_DX>(epi, c, dtype, g, s);
-      case R_O_DX: return launch_epi<R_O_DX>(epi, c, dtype, g, s);
-      case R_FFN_IN_DX: return launch_epi<R_FFN_IN_DX>(epi, c, dtype, g, s);
-      case R_FFN_OUT_DX: return launch_epi<R_FFN_OUT_DX>(epi, c, dtype, g, s);
-      default: return hipErrorInvalidValue;
-    }
-  };
-  // The 256x128 kernel runs one workgroup per CU.  When its tiles leave the
-  // GPU's last round at most half full (LLaMA-7B FFN-in: 8 x 172 = 1376 tiles,
-  // five rounds of 256 and 96), that round is split off along N: the columns
-  // of the whole rounds go to this kernel, the rest to 128x128 tiles, which
-  // spread it over every CU instead of leaving most of them idle.  Each output
-  // column is still computed by one tile, in the same order.
-  if (cfg == C_P256x128_8W && !rope) {
-    const int rt = (a.M + 255) / 256;
-    const long nt = (long)rt * ((a.N + 127) / 128), rem = nt % 256;
-    if (256 % rt == 0 && rem != 0 && rem <= 128) {
-      const int n_main = (int)(nt / 256) * (256 / rt) * 128;
-      if (n_main > 0 && n_main < a.N) {
-        GemmArgs m = a, t = a;
-        m.N = n_main;
-        t.N = a.N - n_main;
-        t.B = static_cast<const bf16*>(a.B) + (long)n_main * a.ldb;
-        // output columns: SwiGLU writes one column per gate/up pair (the stash
-        // keeps the pair at f and half + f); every other epilogue one per column
-        const int oc = epi == Epi::SwiGlu ? n_main / 2 : n_main;
-        t.out = static_cast<bf16*>(a.out) + oc;
-        if (a.out2) t.out2 = static_cast<bf16*>(a.out2) + oc;
-        if (a.bias) t.bias = static_cast<const bf16*>(a.bias) + n_main;
-        if (a.aux) t.aux = static_cast<const bf16*>(a.aux) + n_main;
-        const long tail_tiles = (long)((a.M + 127) / 128) * ((t.N + 127) / 128);
-        const Cfg ct = tail_tiles >= 512 ? C_P128x128_2 : C_P128x128_3;
-        const hipError_t e = go(cfg, m);
-        return e != hipSuccess ? e : go(ct, t);
-      }
-    }
+  switch (role) {
+    case R_QKV_FWD: return launch_epi<R_QKV_FWD>(epi, cfg, dtype, a, s);
+    case R_O_FWD: return launch_epi<R_O_FWD>(epi, cfg, dtype, a, s);
+    case R_FFN_IN_FWD: return launch_epi<R_FFN_IN_FWD>(epi, cfg, dtype, a, s);
+    case R_FFN_OUT_FWD: return launch_epi<R_FFN_OUT_FWD>(epi, cfg, dtype, a, s);
+    case R_QKV_DX: return launch_epi<R_QKV_DX>(epi, cfg, dtype, a, s);
+    case R_O_DX: return launch_epi<R_O_DX>(epi, cfg, dtype, a, s);
+    case R_FFN_IN_DX: return launch_epi<R_FFN_IN_DX>(epi, cfg, dtype, a, s);
+    case R_FFN_OUT_DX: return launch_epi<R_FFN_OUT_DX>(epi, cfg, dtype, a, s);
+    default: return hipErrorInvalidValue;
   }
-  return go(cfg, a);
 }
 
 }  // namespace rg
