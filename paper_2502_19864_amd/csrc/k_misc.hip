@@ -446,19 +446,279 @@ hipError_t launch_mse(int dtype, const void* y, const void* t, long n, void* dy,
 // cross-entropy, mean over the batch.  dy[b, 0, :] = dlogits W_h^T, zero at
 // every other position; the head gradients and the loss are added into
 // gwh / gbh / loss.
-// Workgroup 0 does every sum, so that each result is one thread's sum over
-// the samples in order: the same inputs give the same bits (atomic adds in
-// arrival order would not).  Samples go in chunks of HEAD_CHUNK: one wave
-// per sample for the logits, the softmax and the loss (into LDS), then one
-// thread per feature (in blocks of HEAD_NT features) for the dY rows and the
-// W_h gradient, thread c for the bias gradient of class c and thread 0 for
-// the loss.  The other workgroups
-// zero rows 1..S-1 of every sequence with 16-B stores.
+// Every sum has one order, whatever the workgroups' order: the same inputs give
+// the same bits (atomic adds in arrival order would not).
 constexpr int HEAD_C = 16;        // maximum number of classes
 constexpr int HEAD_NT = 1024;     // threads per workgroup (16 waves)
-constexpr int HEAD_CHUNK = 256;   // samples per pass of workgroup 0
+constexpr int HEAD_CHUNK = 256;   // samples per pass of head_ce_inplace_k
+
+// rows 1 .. S-1 of every sequence of dY, by workgroup z of nz
+template <typename T>
+__device__ __forceinline__ void head_zero_rows(T* dy, int B, int S, int d, int z, int nz, bool nt) {
+  const int vpr = d * (int)sizeof(T) / 16;  // 16-B vectors per row
+  const long nvec = (long)B * (S - 1) * vpr;
+  for (long v = (long)z * HEAD_NT + threadIdx.x; v < nvec; v += (long)nz * HEAD_NT) {
+    const long rr = v / vpr;
+    const long r = (rr / (S - 1)) * S + 1 + rr % (S - 1);
+    st16(reinterpret_cast<uint4*>(dy + r * d) + v % vpr, zero_frag(), nt);
+  }
+}
+
+// per-lane partial logits of K rows over features 8 (lane + 64 j)
+template <typename T, int CN, int K>
+__device__ __forceinline__ void head_dot(const T* const (&yr)[K], const float* wh, int d, int C, int lane,
+                                         float (&lg)[K][CN]) {
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int c = 0; c < CN; ++c) lg[k][c] = 0.f;
+  for (int v = lane; v < d / 8; v += 64) {
+    float yv[K][8];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if constexpr (std::is_same_v<T, bf16>) {
+        unpack_frag(ld_frag(yr[k] + 8 * v), yv[k]);
+      } else {
+        const float4 q0 = reinterpret_cast<const float4*>(yr[k])[2 * v];
+        const float4 q1 = reinterpret_cast<const float4*>(yr[k])[2 * v + 1];
+        yv[k][0] = q0.x; yv[k][1] = q0.y; yv[k][2] = q0.z; yv[k][3] = q0.w;
+        yv[k][4] = q1.x; yv[k][5] = q1.y; yv[k][6] = q1.z; yv[k][7] = q1.w;
+      }
+    }
+    const float* wr = wh + (long)8 * v * C;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int c = 0; c < CN; ++c)
+        if (c < C) {
+          const float wc = wr[e * C + c];
+#pragma unroll
+          for (int k = 0; k < K; ++k) lg[k][c] += yv[k][e] * wc;
+        }
+  }
+}
+
+// from the partial logits of one row: d loss / d logits (0 past C) in lg on
+// every lane, the row's share of the mean loss returned
+template <int CN>
+__device__ __forceinline__ float head_softmax(float (&lg)[CN], const float* bh, int C, int lab, int B) {
+  float mx = -INFINITY;
+#pragma unroll
+  for (int c = 0; c < CN; ++c)
+    if (c < C) {
+      lg[c] = wave_sum(lg[c]) + bh[c];
+      mx = fmaxf(mx, lg[c]);
+    }
+  float se = 0.f, ll = 0.f;
+#pragma unroll
+  for (int c = 0; c < CN; ++c)
+    if (c < C) {
+      se += __expf(lg[c] - mx);
+      if (c == lab) ll = lg[c];
+    }
+#pragma unroll
+  for (int c = 0; c < CN; ++c)
+    lg[c] = c < C ? (__expf(lg[c] - mx) / se - (c == lab ? 1.f : 0.f)) / (float)B : 0.f;
+  return -(ll - mx - __logf(se)) / (float)B;
+}
+
+// Two classes: the first nf workgroups take HEAD_F features each, the others zero rows.  A
+// wave owns every 16th sample: it forms that sample's logits from the whole row
+// (every feature workgroup does so again: the rows are small and in the cache),
+// then its lanes, one feature each, write dY and add to the W_h gradient, so
+// nothing waits on another wave until the sums over the waves, in wave order,
+// at the end.  What the end adds to is loaded at the start.  Bound by latency
+// (one round trip for the rows, one launch): B 32, S 128, d 768 bf16 10.4 -> 5.9
+// us, where one workgroup went through all features after a barrier.
+constexpr int HEAD_F = 64;  // features per workgroup: one per lane
+template <typename T>
+__global__ __launch_bounds__(HEAD_NT) void head_ce2_k(const T* y, int B, int S, int d, const float* wh,
+                                                      const float* bh, const int* labels, T* dy, float* gwh,
+                                                      float* gbh, float* loss, int nf) {
+  constexpr int C = 2, CN = 2;
+  if ((int)blockIdx.x >= nf) {
+    head_zero_rows(dy, B, S, d, (int)blockIdx.x - nf, (int)gridDim.x - nf,
+                   stream_out((long)B * S * d * (long)sizeof(T)));
+    return;
+  }
+  constexpr int NW = HEAD_NT / 64, PAIR = 2;
+  __shared__ float red[NW][HEAD_F][CN];
+  __shared__ float redb[NW][CN + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = threadIdx.x;
+  const int f0 = blockIdx.x * HEAD_F, f = min(f0 + lane, d - 1);
+  const bool fv = f0 + lane < d;
+  const bool gv = t < HEAD_F * C && f0 * C + t < d * C, first = blockIdx.x == 0;
+  const float gold = gv ? gwh[(long)f0 * C + t] : 0.f;
+  const float bold = first && t < C ? gbh[t] : 0.f, lold = first && t == 0 && loss ? *loss : 0.f;
+  float wv[CN], gacc[CN], bacc[CN], lacc = 0.f;
+#pragma unroll
+  for (int c = 0; c < CN; ++c) {
+    wv[c] = wh[(long)f * C + c];
+    gacc[c] = bacc[c] = 0.f;
+  }
+  for (int sm = wave; sm < B; sm += PAIR * NW) {
+    const T* yr[PAIR];
+    float yf[PAIR], lg[PAIR][CN];
+    int lab[PAIR];
+#pragma unroll
+    for (int k = 0; k < PAIR; ++k) {
+      const int smk = min(sm + k * NW, B - 1);
+      yr[k] = y + (long)smk * S * d;
+      yf[k] = St<T>::ld(yr[k], f);
+      lab[k] = labels[smk];
+    }
+    head_dot<T, CN, PAIR>(yr, wh, d, C, lane, lg);
+#pragma unroll
+    for (int k = 0; k < PAIR; ++k) {
+      if (sm + k * NW >= B) break;  // wave-uniform
+      lacc += head_softmax<CN>(lg[k], bh, C, lab[k], B);
+      float g = 0.f;
+#pragma unroll
+      for (int c = 0; c < CN; ++c) {
+        gacc[c] += yf[k] * lg[k][c];
+        bacc[c] += lg[k][c];
+        g += lg[k][c] * wv[c];
+      }
+      if (fv) St<T>::st_nt(dy, (long)(sm + k * NW) * S * d + f, g);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < CN; ++c) red[wave][lane][c] = gacc[c];
+  if (first && lane == 0) {
+#pragma unroll
+    for (int c = 0; c < CN; ++c) redb[wave][c] = bacc[c];
+    redb[wave][CN] = lacc;
+  }
+  __syncthreads();
+  if (gv) {
+    float g = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) g += red[w][t / C][t % C];
+    gwh[(long)f0 * C + t] = gold + g;
+  }
+  if (first && t < C) {
+    float b = 0.f, l = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      b += redb[w][t];
+      l += redb[w][CN];
+    }
+    gbh[t] = bold + b;
+    if (t == 0 && loss) *loss = lold + l;
+  }
+}
+
+// Up to 16 classes, the same division of the features.  The logits of 16 samples
+// at a time are one 16x16 tile of MFMA 16x16x4 f32 (classes x samples), its K, the
+// features, dealt to the 16 waves in blocks of 16; the waves' sums are added in
+// LDS, 16 lanes share a sample for the softmax, then wave = sample and lane =
+// feature as above.  One wave per sample read all of W_h for each, at a
+// 512-B lane stride: B 128, S 16, d 4096, 16 classes 3947 -> 96 us, B 8,
+// S 512, d 2048, 3 classes 35.5 -> 10.4 us.
+template <typename T>
+__global__ __launch_bounds__(HEAD_NT) void head_ce_many_k(const T* y, int B, int S, int d, const float* wh,
+                                                          const float* bh, int C, const int* labels, T* dy,
+                                                          float* gwh, float* gbh, float* loss, int nf) {
+  if ((int)blockIdx.x >= nf) {
+    head_zero_rows(dy, B, S, d, (int)blockIdx.x - nf, (int)gridDim.x - nf,
+                   stream_out((long)B * S * d * (long)sizeof(T)));
+    return;
+  }
+  constexpr int NW = HEAD_NT / 64, CN = HEAD_C;
+  static_assert(NW == 16 && CN == 16, "16 samples x 16 classes, one sample per wave");
+  __shared__ float part[NW][CN][17];
+  __shared__ float sdl[NW][CN];
+  __shared__ float sls[NW];
+  __shared__ float red[NW][HEAD_F][CN];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = threadIdx.x, l16 = lane & 15, grp = lane >> 4;
+  const int f0 = blockIdx.x * HEAD_F, f = min(f0 + lane, d - 1);
+  const bool fv = f0 + lane < d;
+  const bool gv = t < HEAD_F * C && f0 * C + t < d * C, first = blockIdx.x == 0;
+  const float gold = gv ? gwh[(long)f0 * C + t] : 0.f;
+  const float bold = first && t < C ? gbh[t] : 0.f, lold = first && t == 0 && loss ? *loss : 0.f;
+  float wv[CN], gacc[CN], bacc = 0.f, lacc = 0.f;
+#pragma unroll
+  for (int c = 0; c < CN; ++c) {
+    wv[c] = c < C ? wh[(long)f * C + c] : 0.f;
+    gacc[c] = 0.f;
+  }
+  const int cls = min(l16, C - 1);
+  for (int b0 = 0; b0 < B; b0 += NW) {
+    const float yf = St<T>::ld(y, (long)min(b0 + wave, B - 1) * S * d + f);
+    // samples past the batch read its last row, features past d the row's first: masked
+    const T* yr = y + (long)min(b0 + l16, B - 1) * S * d;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int kb = wave * 16; kb < d; kb += 16 * NW) {
+      const bool in = kb + 4 * grp < d;  // d is a multiple of 8: pieces of 4 are whole or absent
+      const int k = in ? kb + 4 * grp : 0;
+      float yv[4], w[4];
+      St<T>::ld4(yr, k, yv);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = wh[(long)(k + e) * C + cls];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in && l16 < C ? w[e] : 0.f, in ? yv[e] : 0.f, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave][4 * grp + r][l16] = acc[r];  // [class][sample]
+    __syncthreads();
+    if (t < NW * CN) {
+      const int sm = t / CN, c = t % CN, lab = labels[min(b0 + sm, B - 1)];
+      float lg = c < C ? bh[c] : 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) lg += part[w][c][sm];
+      float mx = c < C ? lg : -INFINITY;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      const float e = c < C ? __expf(lg - mx) : 0.f;
+      float se = e, ll = c == lab ? lg : 0.f;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) {
+        se += __shfl_xor(se, o, 64);
+        ll += __shfl_xor(ll, o, 64);
+      }
+      const bool sv = b0 + sm < B && c < C;
+      sdl[sm][c] = sv ? (e / se - (c == lab ? 1.f : 0.f)) / (float)B : 0.f;
+      if (c == 0) sls[sm] = sv ? -(ll - mx - __logf(se)) / (float)B : 0.f;
+    }
+    __syncthreads();
+    float g = 0.f;
+#pragma unroll
+    for (int c = 0; c < CN; ++c) {
+      const float dl = sdl[wave][c];
+      gacc[c] += yf * dl;
+      g += dl * wv[c];
+    }
+    if (fv && b0 + wave < B) St<T>::st_nt(dy, (long)(b0 + wave) * S * d + f, g);
+    if (first && t < C)
+#pragma unroll
+      for (int sm = 0; sm < NW; ++sm) {
+        bacc += sdl[sm][t];
+        lacc += sls[sm];
+      }
+  }
+#pragma unroll
+  for (int c = 0; c < CN; ++c) red[wave][lane][c] = gacc[c];
+  __syncthreads();
+  if (gv) {
+    float g = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) g += red[w][t / C][t % C];
+    gwh[(long)f0 * C + t] = gold + g;
+  }
+  if (first && t < C) gbh[t] = bold + bacc;
+  if (first && t == 0 && loss) *loss = lold + lacc;
+}
+
+// dY in the place of y: one workgroup for all features, so that no row is
+// written before its logits are formed.  Samples go in chunks of HEAD_CHUNK: one
+// wave per sample for the logits, the softmax and the loss (into LDS), then one
+// thread per feature (in blocks of HEAD_NT features) for the dY rows and the
+// W_h gradient, thread c for the bias gradient of class c and thread 0 for
+// the loss.  The other workgroups zero rows 1..S-1 of every sequence.
 template <typename T, int CN>  // CN: class count bound, compile time (the loops over classes unroll)
-__global__ __launch_bounds__(HEAD_NT) void head_ce_k(const T* y, int B, int S, int d, const float* wh,
+__global__ __launch_bounds__(HEAD_NT) void head_ce_inplace_k(const T* y, int B, int S, int d, const float* wh,
                                                      const float* bh, int C_, const int* labels, T* dy, float* gwh,
                                                      float* gbh, float* loss) {
   // the two-class instantiation runs only with C == 2: a compile-time class count leaves
@@ -466,14 +726,7 @@ __global__ __launch_bounds__(HEAD_NT) void head_ce_k(const T* y, int B, int S, i
   const int C = CN == 2 ? 2 : C_;
   const bool nt = stream_out((long)B * S * d * (long)sizeof(T));  // dY streamed (common.h)
   if (blockIdx.x > 0) {
-    const int nz = gridDim.x - 1, z = blockIdx.x - 1;
-    const int vpr = d * (int)sizeof(T) / 16;  // 16-B vectors per row
-    const long nvec = (long)B * (S - 1) * vpr;
-    for (long v = (long)z * HEAD_NT + threadIdx.x; v < nvec; v += (long)nz * HEAD_NT) {
-      const long rr = v / vpr;
-      const long r = (rr / (S - 1)) * S + 1 + rr % (S - 1);
-      st16(reinterpret_cast<uint4*>(dy + r * d) + v % vpr, zero_frag(), nt);
-    }
+    head_zero_rows(dy, B, S, d, (int)blockIdx.x - 1, (int)gridDim.x - 1, nt);
     return;
   }
   constexpr int NW = HEAD_NT / 64;
@@ -495,57 +748,15 @@ __global__ __launch_bounds__(HEAD_NT) void head_ce_k(const T* y, int B, int S, i
         yr[k] = y + (long)(b0 + smk[k]) * S * d;
       }
       float lg[PAIR][CN];
-#pragma unroll
-      for (int k = 0; k < PAIR; ++k)
-#pragma unroll
-        for (int c = 0; c < CN; ++c) lg[k][c] = 0.f;
-      for (int v = lane; v < d / 8; v += 64) {
-        float yv[PAIR][8];
-#pragma unroll
-        for (int k = 0; k < PAIR; ++k) {
-          if constexpr (std::is_same_v<T, bf16>) {
-            unpack_frag(ld_frag(yr[k] + 8 * v), yv[k]);
-          } else {
-            const float4 q0 = reinterpret_cast<const float4*>(yr[k])[2 * v];
-            const float4 q1 = reinterpret_cast<const float4*>(yr[k])[2 * v + 1];
-            yv[k][0] = q0.x; yv[k][1] = q0.y; yv[k][2] = q0.z; yv[k][3] = q0.w;
-            yv[k][4] = q1.x; yv[k][5] = q1.y; yv[k][6] = q1.z; yv[k][7] = q1.w;
-          }
-        }
-        const float* wr = wh + (long)8 * v * C;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int c = 0; c < CN; ++c)
-            if (c < C) {
-              const float wc = wr[e * C + c];
-#pragma unroll
-              for (int k = 0; k < PAIR; ++k) lg[k][c] += yv[k][e] * wc;
-            }
-      }
+      head_dot<T, CN, PAIR>(yr, wh, d, C, lane, lg);
 #pragma unroll
       for (int k = 0; k < PAIR; ++k) {
         if (sm + k * NW >= nb) break;  // wave-uniform
-        const int lab = labels[b0 + smk[k]];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int c = 0; c < CN; ++c)
-          if (c < C) {
-            lg[k][c] = wave_sum(lg[k][c]) + bh[c];
-            mx = fmaxf(mx, lg[k][c]);
-          }
-        float se = 0.f, ll = 0.f;
-#pragma unroll
-        for (int c = 0; c < CN; ++c)
-          if (c < C) {
-            se += __expf(lg[k][c] - mx);
-            if (c == lab) ll = lg[k][c];
-          }
+        const float l = head_softmax<CN>(lg[k], bh, C, labels[b0 + smk[k]], B);
         if (lane == 0) {
-          sls[smk[k]] = -(ll - mx - __logf(se)) / (float)B;
+          sls[smk[k]] = l;
 #pragma unroll
-          for (int c = 0; c < CN; ++c)
-            sdl[smk[k]][c] = c < C ? (__expf(lg[k][c] - mx) / se - (c == lab ? 1.f : 0.f)) / (float)B : 0.f;
+          for (int c = 0; c < CN; ++c) sdl[smk[k]][c] = lg[k][c];
         }
       }
     }
@@ -621,22 +832,28 @@ hipError_t launch_head_ce(int dtype, const void* y, int B, int S, int d, const f
     return hipErrorInvalidValue;
   const long nvec = (long)B * (S - 1) * (long)(d * es / 16);
   const int nz = (int)std::min<long>(255, (nvec + HEAD_NT - 1) / HEAD_NT);
-  const dim3 grid(1 + nz), block(HEAD_NT);
-  if (dtype == DT_BF16) {
-    if (C == 2)
-      RG_LAUNCH((head_ce_k<bf16, 2>), grid, block, 0, s, (const bf16*)y, B, S, d, wh, bh, C, labels, (bf16*)dy,
-                gwh, gbh, loss);
+  const char* yb = static_cast<const char*>(y);
+  const char* db = static_cast<const char*>(dy);
+  const size_t bytes = (size_t)B * S * d * es;
+  const bool overlap = yb < db + bytes && db < yb + bytes;
+  const int nf = overlap ? 1 : (d + HEAD_F - 1) / HEAD_F;
+  const dim3 grid(nf + nz), block(HEAD_NT);
+  auto go = [&](auto T0) {
+    using T = decltype(T0);
+    const T* yt = static_cast<const T*>(y);
+    T* dt = static_cast<T*>(dy);
+    if (overlap && C == 2)
+      RG_LAUNCH((head_ce_inplace_k<T, 2>), grid, block, 0, s, yt, B, S, d, wh, bh, C, labels, dt, gwh, gbh, loss);
+    else if (overlap)
+      RG_LAUNCH((head_ce_inplace_k<T, HEAD_C>), grid, block, 0, s, yt, B, S, d, wh, bh, C, labels, dt, gwh, gbh,
+                loss);
+    else if (C == 2)
+      RG_LAUNCH((head_ce2_k<T>), grid, block, 0, s, yt, B, S, d, wh, bh, labels, dt, gwh, gbh, loss, nf);
     else
-      RG_LAUNCH((head_ce_k<bf16, HEAD_C>), grid, block, 0, s, (const bf16*)y, B, S, d, wh, bh, C, labels,
-                (bf16*)dy, gwh, gbh, loss);
-  } else {
-    if (C == 2)
-      RG_LAUNCH((head_ce_k<float, 2>), grid, block, 0, s, (const float*)y, B, S, d, wh, bh, C, labels, (float*)dy,
-                gwh, gbh, loss);
-    else
-      RG_LAUNCH((head_ce_k<float, HEAD_C>), grid, block, 0, s, (const float*)y, B, S, d, wh, bh, C, labels,
-                (float*)dy, gwh, gbh, loss);
-  }
+      RG_LAUNCH((head_ce_many_k<T>), grid, block, 0, s, yt, B, S, d, wh, bh, C, labels, dt, gwh, gbh, loss, nf);
+  };
+  if (dtype == DT_BF16) go(bf16{});
+  else go(float{});
   return hipGetLastError();
 }
 
