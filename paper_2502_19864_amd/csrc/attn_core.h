@@ -40,24 +40,28 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int j) {
 // position of register value r within a 32-wide score block for this lane half
 __device__ __forceinline__ int perm_pos(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
 
-// Writes a 32-row x DH accumulator (transposed layout: lane = row, dims
-// 8*(r/4) + 4*half + r%4 of block db) scaled, optionally un-rotated.
+// Rotates a 32-row x DH accumulator (transposed layout: lane = row, dims
+// 8*(r/4) + 4*half + r%4 of block db) back by position pos.
+template <int DH>
+__device__ __forceinline__ void unrotate(f32x16 (&acc)[DH / 32], int pos, const float2* rtab, int half) {
+#pragma unroll
+  for (int db = 0; db < DH / 64; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = db * 32 + perm_pos(r, half);
+      float cs, sn;
+      rope_cs(rtab, pos, i, DH, &cs, &sn);
+      const float d1 = acc[db][r], d2 = acc[db + DH / 64][r];
+      acc[db][r] = d1 * cs + d2 * sn;
+      acc[db + DH / 64][r] = d2 * cs - d1 * sn;
+    }
+}
+
+// Writes such an accumulator scaled, optionally un-rotated.
 template <int DH>
 __device__ __forceinline__ void store_rows(f32x16 (&acc)[DH / 32], float scale, bool unrot, int pos,
                                            const float2* rtab, int half, bf16* dst) {
-  if (unrot) {
-#pragma unroll
-    for (int db = 0; db < DH / 64; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = db * 32 + perm_pos(r, half);
-        float cs, sn;
-        rope_cs(rtab, pos, i, DH, &cs, &sn);
-        const float d1 = acc[db][r], d2 = acc[db + DH / 64][r];
-        acc[db][r] = d1 * cs + d2 * sn;
-        acc[db + DH / 64][r] = d2 * cs - d1 * sn;
-      }
-  }
+  if (unrot) unrotate<DH>(acc, pos, rtab, half);
 #pragma unroll
   for (int db = 0; db < DH / 32; ++db)
 #pragma unroll
@@ -69,14 +73,14 @@ __device__ __forceinline__ void store_rows(f32x16 (&acc)[DH / 32], float scale, 
     }
 }
 
-// The same rows (unscaled, not rotated) through LDS: each lane writes its row
+// The same rows (not rotated), the first n of them, through LDS: each lane writes its row
 // into the 32 staging rows (pitch DH + 8, private to the wave), then each
 // store instruction writes whole rows, 16 B per lane (8 rows of 128 B at DH
 // 64), so the stores can be streamed (st16).  One wave's LDS operations run in
 // order, so the reads see the writes without a barrier.
 template <int DH>
 __device__ __forceinline__ void store_rows_staged(const f32x16 (&acc)[DH / 32], float scale, int half, int lane,
-                                                  bf16* stage, bf16* dst0, long ld, bool nt) {
+                                                  bf16* stage, bf16* dst0, long ld, bool nt, int n = 32) {
   const int l32 = lane & 31;
 #pragma unroll
   for (int db = 0; db < DH / 32; ++db)
@@ -91,7 +95,7 @@ __device__ __forceinline__ void store_rows_staged(const f32x16 (&acc)[DH / 32], 
 #pragma unroll
   for (int k = lane; k < 32 * CPR; k += 64) {
     const int row = k / CPR, c = k % CPR;
-    st16(dst0 + row * ld + 8 * c, ld_frag(stage + row * (DH + 8) + 8 * c), nt);
+    if (row < n) st16(dst0 + row * ld + 8 * c, ld_frag(stage + row * (DH + 8) + 8 * c), nt);
   }
 }
 

@@ -72,54 +72,83 @@ struct TileLoad {
   }
 };
 
-// Two tiles (e.g. K and V) with one memory round trip: both tiles' global
-// loads are issued before the first LDS store; the first is rotated when rot0.
-template <int DH, int NT>
-__device__ __forceinline__ void load_tile_pair(const bf16* src0, int ld0, int col0, bool rot0, bf16* dst0,
-                                               const bf16* src1, int ld1, int col1, bf16* dst1, int b, int S,
-                                               int r0, const float2* rtab) {
-  TileLoad<DH, NT> t0, t1;
-  t0.issue(src0, ld0, col0, b, S, r0);
-  t1.issue(src1, ld1, col1, b, S, r0);
-  t0.store(dst0, rot0, S, r0, rtab);
-  t1.store(dst1, false, S, r0, rtab);
-}
-
 // Q and K need the rotation as they are loaded (it is not already in qkv)
 __device__ __forceinline__ bool rot_load(const AttnArgs& a) { return a.rope && !a.rope_in_qkv; }
 
 // Fragments (B operand, k = head dim) of one row held by this lane: dims
-// 16s + 8*(lane/32) + v, rotated when rot.
+// 16s + 8*(lane/32) + v, zero when !valid (src is a valid row even then: the loads are
+// unconditional and issued together, the values masked afterwards).
 template <int DH>
-__device__ __forceinline__ void load_row_frags(const bf16* src, int pos, bool valid, bool rot,
-                                               const float2* rtab, int half, bf16x8 f[DH / 16]) {
-  // src is a valid row even when !valid (callers clamp it): the loads are unconditional
-  // and issued together, the values masked afterwards
-  float x[DH / 16][8];
-  bf16x8 raw[DH / 16];
+__device__ __forceinline__ void load_row_frags(const bf16* src, bool valid, int half, bf16x8 f[DH / 16]) {
 #pragma unroll
-  for (int s = 0; s < DH / 16; ++s) raw[s] = ld_frag(src + 16 * s + 8 * half);
+  for (int s = 0; s < DH / 16; ++s) f[s] = ld_frag(src + 16 * s + 8 * half);
 #pragma unroll
-  for (int s = 0; s < DH / 16; ++s) {
-    unpack_frag(raw[s], x[s]);
+  for (int s = 0; s < DH / 16; ++s)
+    if (!valid) f[s] = zero_frag();
+}
+
+// ---------------------------------------------------------------- tiles by DMA
+// A [R x DH] tile goes global -> LDS by DMA, rows unpadded (the DMA writes 1 KB runs):
+// 16-B chunk c of row r sits at c ^ swz(r).  The swizzle has to serve two reads:
+// ld_frag of one chunk of 16 consecutive rows (all sixteen must land on
+// different 16-B slots of the 256 B that one pass of the LDS covers), and the
+// transpose read of four chunks of four consecutive rows (each row on a 64-B
+// group of its own; rows padded by 16 B, as before, put all four on two groups).
+template <int DH>
+__device__ __forceinline__ int swz(int r) {
+  return DH == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
+// rows r0 .. r0 + R - 1 (r0 < S; rows past S - 1 read that row: their scores are masked)
+// of column col; the caller waits with tiles_ready
+template <int DH, int R, int NW>
+__device__ __forceinline__ void tile_dma(const bf16* src, int ld, int col, int b, int S, int r0, bf16* dst) {
+  constexpr int CPR = DH / 8, RPI = 64 / CPR;
+  static_assert(R % (RPI * NW) == 0, "whole DMA instructions per wave");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bf16* base = src + ((long)b * S + r0) * ld + col;
 #pragma unroll
-    for (int v = 0; v < 8; ++v) x[s][v] = valid ? x[s][v] : 0.f;
+  for (int i = 0; i < R / (RPI * NW); ++i) {
+    const int r = (i * NW + wave) * RPI + lane / CPR, c = (lane % CPR) ^ swz<DH>(r);
+    dma16_m0(base, (uint32_t)((min(r, S - 1 - r0) * ld + c * 8) * 2), lds_addr(dst) + (i * NW + wave) * 1024);
   }
-  if (rot && valid) {
+}
+// this wave's DMAs have landed and its LDS reads are done, then everybody's
+__device__ __forceinline__ void tiles_ready() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// Element offsets of this lane's reads in such a tile: row[s] for the chunk of
+// dims 16s + 8*half of row lane%32, tr[h][db] for the two halves of perm_frag's
+// transpose read of block db (rows + kb*32 (+ 16j): a multiple of 16, which the
+// swizzle does not see, so blocks are reached by constant offsets).
+template <int DH>
+struct TileRead {
+  int row[DH / 16], tr[2][DH / 32];
+  __device__ __forceinline__ explicit TileRead(int lane) {
+    const int l32 = lane & 31, half = lane >> 5, g = lane >> 4, r = lane & 15;
 #pragma unroll
-    for (int s = 0; s < DH / 32; ++s)
+    for (int s = 0; s < DH / 16; ++s) row[s] = l32 * DH + (((2 * s + half) ^ swz<DH>(l32)) * 8);
 #pragma unroll
-      for (int v = 0; v < 8; ++v) {
-        float cs, sn;
-        rope_cs(rtab, pos, 16 * s + 8 * half + v, DH, &cs, &sn);
-        const float a = x[s][v], bb = x[s + DH / 32][v];
-        x[s][v] = a * cs - bb * sn;
-        x[s + DH / 32][v] = bb * cs + a * sn;
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int db = 0; db < DH / 32; ++db) {
+        const int rr = 4 * (g >> 1) + 8 * h + (r >> 2), c = db * 4 + 2 * (g & 1) + ((r & 3) >> 1);
+        tr[h][db] = rr * DH + ((c ^ swz<DH>(rr)) * 8) + 4 * (r & 1);
       }
   }
-#pragma unroll
-  for (int s = 0; s < DH / 16; ++s) f[s] = pack_frag(x[s]);
-}
+  // fragment of rows kb*32 + lane%32, dims 16s + 8*half + 0..7
+  __device__ __forceinline__ bf16x8 frag(const bf16* tile, int kb, int s) const {
+    return ld_frag(tile + row[s] + kb * 32 * DH);
+  }
+  // the same operand as perm_frag
+  __device__ __forceinline__ bf16x8 perm(const bf16* tile, int db, int kb, int j) const {
+    const bf16* t = tile + (kb * 32 + 16 * j) * DH;
+    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(t + tr[0][db])));
+    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(t + tr[1][db])));
+    return __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+  }
+};
 
 // Causal tiles do unequal work: query tile t of nq takes t + 1 key tiles (the dK/dV
 // pass: key block j takes nq - j query tiles).  At d_h = 128 a workgroup fills its CU,
@@ -141,10 +170,21 @@ __device__ __forceinline__ void heavy_first(int lin, int nq, int nbh, int& rank,
   bh = x * per + o % per;
 }
 
-template <int DH, bool CAUSAL, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_fwd_bf16(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16 sK[KT * (DH + 8)];
-  __shared__ __attribute__((aligned(16))) bf16 sV[KT * (DH + 8)];
+// Forward and the two backward passes for more than one tile.  Each works
+// through tiles of KR rows of the other side, two deep in LDS by DMA (one barrier
+// per tile, no registers held for the loads), and skips, wave by wave, blocks
+// that the causal mask or the sequence's end leaves empty.  KR 64 and no staging
+// registers keep d_head 128 within two waves per SIMD (one before: nothing
+// overlapped the softmax with MFMAs and LDS reads).  Results leave through LDS as
+// whole rows.
+// Before -> after, us: 2048 tokens of 512, 32 heads of 128, causal: forward 43 -> 23,
+// dQ 56 -> 40, dK/dV 71 -> 65; 4096 tokens of 256, 16 heads of 64: 15.8 -> 13.6,
+// 20.4 -> 20.4, 28.6 -> 21.4.
+template <int DH, bool CAUSAL, int NW, int KR>
+__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_bf16(AttnArgs a) {
+  constexpr int TILE = KR * DH;
+  __shared__ __attribute__((aligned(1024))) bf16 sm[4 * TILE];  // [buffer][K, V]
+  static_assert(4 * TILE >= NW * 32 * (DH + 8), "the O rows fit the tiles' space");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
   int qb, bh;
   if (CAUSAL) {
@@ -156,16 +196,19 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_bf16(AttnArgs a) {
     bh = blk / gridDim.x;
   }
   const int b = bh / a.H, hd = bh % a.H, S = a.S;
-  const int q = qb * (32 * NW) + wave * 32 + l32;
+  const int q0 = qb * (32 * NW) + wave * 32, q = q0 + l32;  // this wave's first query, this lane's
   const bool qv = q < S;
-  const int d = a.H * DH;
-  const float2* rtab = a.rope_tab;
   const float sl2 = kLog2e * rsqrtf((float)DH);
   const bf16* qkv = static_cast<const bf16*>(a.qkv);
-
+  const TileRead<DH> rd(lane);
+  auto issue = [&](int kt) {
+    bf16* dst = sm + (kt & 1) * 2 * TILE;
+    tile_dma<DH, KR, NW>(qkv, a.ld_qkv, a.qkv_ko + hd * a.qkv_hs, b, S, kt * KR, dst);
+    tile_dma<DH, KR, NW>(qkv, a.ld_qkv, a.qkv_vo + hd * a.qkv_hs, b, S, kt * KR, dst + TILE);
+  };
+  issue(0);
   bf16x8 qf[DH / 16];
-  load_row_frags<DH>(qkv + (long)(b * S + (qv ? q : 0)) * a.ld_qkv + hd * a.qkv_hs, q, qv, rot_load(a),
-                     rtab, half, qf);
+  load_row_frags<DH>(qkv + (long)(b * S + (qv ? q : 0)) * a.ld_qkv + hd * a.qkv_hs, qv, half, qf);
 
   f32x16 oacc[DH / 32];
 #pragma unroll
@@ -175,47 +218,38 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_bf16(AttnArgs a) {
   float mrun = -INFINITY, lrun = 0.f;
 
   const int qlast = min(S - 1, qb * (32 * NW) + 32 * NW - 1);
-  const int nkt = CAUSAL ? qlast / KT + 1 : (S + KT - 1) / KT;
-  // the next K/V tile's global loads are in flight (in registers) while the
-  // current tile is computed on
-  TileLoad<DH, 64 * NW> tk, tv;
-  tk.issue(qkv, a.ld_qkv, a.qkv_ko + hd * a.qkv_hs, b, S, 0);
-  tv.issue(qkv, a.ld_qkv, a.qkv_vo + hd * a.qkv_hs, b, S, 0);
+  const int nkt = CAUSAL ? qlast / KR + 1 : (S + KR - 1) / KR;
   for (int kt = 0; kt < nkt; ++kt) {
-    __syncthreads();
-    tk.store(sK, rot_load(a), S, kt * KT, rtab);
-    tv.store(sV, false, S, kt * KT, rtab);
-    __syncthreads();
-    if (kt + 1 < nkt) {
-      tk.issue(qkv, a.ld_qkv, a.qkv_ko + hd * a.qkv_hs, b, S, (kt + 1) * KT);
-      tv.issue(qkv, a.ld_qkv, a.qkv_vo + hd * a.qkv_hs, b, S, (kt + 1) * KT);
-    }
-    f32x16 sc[KT / 32];
+    tiles_ready();
+    if (kt + 1 < nkt) issue(kt + 1);
+    if (q0 >= S || (CAUSAL && kt * KR > q0 + 31)) continue;  // wave-uniform: nothing to do in this tile
+    const bf16* sK = sm + (kt & 1) * 2 * TILE;
+    const bf16* sV = sK + TILE;
+    f32x16 sc[KR / 32];
 #pragma unroll
-    for (int kb = 0; kb < KT / 32; ++kb) {
+    for (int kb = 0; kb < KR / 32; ++kb) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) sc[kb][r] = 0.f;
 #pragma unroll
-      for (int s = 0; s < DH / 16; ++s)
-        sc[kb] = mfma32(ld_frag(sK + (kb * 32 + l32) * (DH + 8) + 16 * s + 8 * half), qf[s], sc[kb]);
+      for (int s = 0; s < DH / 16; ++s) sc[kb] = mfma32(rd.frag(sK, kb, s), qf[s], sc[kb]);
     }
     // the row max on the raw scores (the scale is positive), the scale folded
     // into the exponent's FMA; masking only where a key can be out of range
     // or in the future
     float mx = -INFINITY;
-    if (CAUSAL || (kt + 1) * KT > S) {
+    if ((CAUSAL && (kt + 1) * KR - 1 > q0) || (kt + 1) * KR > S) {
 #pragma unroll
-      for (int kb = 0; kb < KT / 32; ++kb)
+      for (int kb = 0; kb < KR / 32; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int key = kt * KT + kb * 32 + perm_pos(r, half);
+          const int key = kt * KR + kb * 32 + perm_pos(r, half);
           const bool ok = key < S && (!CAUSAL || key <= q);
           sc[kb][r] = ok ? sc[kb][r] : -INFINITY;
           mx = fmaxf(mx, sc[kb][r]);
         }
     } else {
 #pragma unroll
-      for (int kb = 0; kb < KT / 32; ++kb)
+      for (int kb = 0; kb < KR / 32; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kb][r]);
     }
@@ -224,7 +258,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_bf16(AttnArgs a) {
     const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);  // 0 on the first tile
     float rs = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < KT / 32; ++kb)
+    for (int kb = 0; kb < KR / 32; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         sc[kb][r] = __builtin_amdgcn_exp2f(fmaf(sc[kb][r], sl2, -mnew));
@@ -238,27 +272,28 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_bf16(AttnArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
 #pragma unroll
-    for (int kb = 0; kb < KT / 32; ++kb)
+    for (int kb = 0; kb < KR / 32; ++kb)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const bf16x8 pf = pack8(sc[kb], j);
 #pragma unroll
-        for (int db = 0; db < DH / 32; ++db)
-          oacc[db] = mfma32(perm_frag<DH>(sV, db, kb, j, lane), pf, oacc[db]);
+        for (int db = 0; db < DH / 32; ++db) oacc[db] = mfma32(rd.perm(sV, db, kb, j), pf, oacc[db]);
       }
   }
-  if (qv) {
-    bf16* o = static_cast<bf16*>(a.o) + (long)(b * S + q) * a.ld_o + hd * DH;
-    store_rows<DH>(oacc, 1.f / lrun, false, q, nullptr, half, o);
-    if (half == 0) a.lse[(long)bh * S + q] = mrun + log2f(lrun);
-  }
+  tiles_ready();  // the tiles' space now takes the O rows
+  if (q0 >= S) return;
+  store_rows_staged<DH>(oacc, 1.f / lrun, half, lane, sm + wave * 32 * (DH + 8),
+                        static_cast<bf16*>(a.o) + (long)(b * S + q0) * a.ld_o + hd * DH, a.ld_o,
+                        stream_out((long)a.B * S * a.H * DH * 2), S - q0);
+  if (qv && half == 0) a.lse[(long)bh * S + q] = mrun + log2f(lrun);
 }
 
 // dQ pass (lane = query); also writes D = rowsum(dO * O)
-template <int DH, bool CAUSAL, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 64 ? 2 : 1))) void attn_bwd_dq_bf16(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16 sK[KT * (DH + 8)];
-  __shared__ __attribute__((aligned(16))) bf16 sV[KT * (DH + 8)];
+template <int DH, bool CAUSAL, int NW, int KR>
+__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_bf16(AttnArgs a) {
+  constexpr int TILE = KR * DH;
+  __shared__ __attribute__((aligned(1024))) bf16 sm[4 * TILE];  // [buffer][K, V]
+  static_assert(4 * TILE >= NW * 32 * (DH + 8), "the dQ rows fit the tiles' space");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
   int qb, bh;
   if (CAUSAL) {
@@ -270,30 +305,29 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
     bh = blk / gridDim.x;
   }
   const int b = bh / a.H, hd = bh % a.H, S = a.S;
-  const int q = qb * (32 * NW) + wave * 32 + l32;
+  const int q0 = qb * (32 * NW) + wave * 32, q = q0 + l32;
   const bool qv = q < S;
-  const int d = a.H * DH;
-  const float2* rtab = a.rope_tab;
   const float scale = rsqrtf((float)DH), sl2 = kLog2e * scale;
   const bf16* qkv = static_cast<const bf16*>(a.qkv);
   const long qrow = (long)(b * S + (qv ? q : 0));
-
+  const TileRead<DH> rd(lane);
+  auto issue = [&](int kt) {
+    bf16* dst = sm + (kt & 1) * 2 * TILE;
+    tile_dma<DH, KR, NW>(qkv, a.ld_qkv, a.qkv_ko + hd * a.qkv_hs, b, S, kt * KR, dst);
+    tile_dma<DH, KR, NW>(qkv, a.ld_qkv, a.qkv_vo + hd * a.qkv_hs, b, S, kt * KR, dst + TILE);
+  };
+  issue(0);
   bf16x8 qf[DH / 16], df[DH / 16];
-  load_row_frags<DH>(qkv + qrow * a.ld_qkv + hd * a.qkv_hs, q, qv, rot_load(a), rtab, half, qf);
-  load_row_frags<DH>(static_cast<const bf16*>(a.dout) + qrow * a.ld_do + hd * DH, q, qv, false,
-                     nullptr, half, df);
+  load_row_frags<DH>(qkv + qrow * a.ld_qkv + hd * a.qkv_hs, qv, half, qf);
+  load_row_frags<DH>(static_cast<const bf16*>(a.dout) + qrow * a.ld_do + hd * DH, qv, half, df);
   float dsum = 0.f;
   {
-    const bf16* orow = static_cast<const bf16*>(a.o) + qrow * a.ld_o + hd * DH;
-    bf16x8 oraw[DH / 16];  // qrow is clamped: unconditional loads, masked after
-#pragma unroll
-    for (int s = 0; s < DH / 16; ++s) oraw[s] = ld_frag(orow + 16 * s + 8 * half);
+    bf16x8 of[DH / 16];
+    load_row_frags<DH>(static_cast<const bf16*>(a.o) + qrow * a.ld_o + hd * DH, qv, half, of);
 #pragma unroll
     for (int s = 0; s < DH / 16; ++s) {
       float ov[8], dv[8];
-      unpack_frag(oraw[s], ov);
-#pragma unroll
-      for (int v = 0; v < 8; ++v) ov[v] = qv ? ov[v] : 0.f;
+      unpack_frag(of[s], ov);
       unpack_frag(df[s], dv);
 #pragma unroll
       for (int v = 0; v < 8; ++v) dsum += ov[v] * dv[v];
@@ -311,37 +345,32 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
     for (int r = 0; r < 16; ++r) dq[i][r] = 0.f;
 
   const int qlast = min(S - 1, qb * (32 * NW) + 32 * NW - 1);
-  const int nkt = CAUSAL ? qlast / KT + 1 : (S + KT - 1) / KT;
-  // the next K/V tile's global loads are in flight while the current one is used
-  TileLoad<DH, 64 * NW> tk, tv;
-  tk.issue(qkv, a.ld_qkv, a.qkv_ko + hd * a.qkv_hs, b, S, 0);
-  tv.issue(qkv, a.ld_qkv, a.qkv_vo + hd * a.qkv_hs, b, S, 0);
+  const int nkt = CAUSAL ? qlast / KR + 1 : (S + KR - 1) / KR;
   for (int kt = 0; kt < nkt; ++kt) {
-    // every query of the workgroup and every key of the tile in range, no causal mask
-    const bool full = !CAUSAL && (qb + 1) * (32 * NW) <= S && (kt + 1) * KT <= S;
-    __syncthreads();
-    tk.store(sK, rot_load(a), S, kt * KT, rtab);
-    tv.store(sV, false, S, kt * KT, rtab);
-    __syncthreads();
-    if (kt + 1 < nkt) {
-      tk.issue(qkv, a.ld_qkv, a.qkv_ko + hd * a.qkv_hs, b, S, (kt + 1) * KT);
-      tv.issue(qkv, a.ld_qkv, a.qkv_vo + hd * a.qkv_hs, b, S, (kt + 1) * KT);
-    }
+    tiles_ready();
+    if (kt + 1 < nkt) issue(kt + 1);
+    if (q0 >= S) continue;
+    const bf16* sK = sm + (kt & 1) * 2 * TILE;
+    const bf16* sV = sK + TILE;
     // one key block at a time (not unrolled): keeps the kernel within the
-    // registers of two waves per SIMD, so a (batch, head) grid fits one round
+    // registers of two waves per SIMD
 #pragma unroll 1
-    for (int kb = 0; kb < KT / 32; ++kb) {
+    for (int kb = 0; kb < KR / 32; ++kb) {
+      const int k0 = kt * KR + kb * 32;
+      if (k0 >= S || (CAUSAL && k0 > q0 + 31)) break;  // wave-uniform
+      // every query and key of the block in range, none masked
+      const bool full = q0 + 32 <= S && k0 + 32 <= S && (!CAUSAL || k0 + 31 <= q0);
       f32x16 st, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) st[r] = dp[r] = 0.f;
 #pragma unroll
       for (int s = 0; s < DH / 16; ++s) {
-        st = mfma32(ld_frag(sK + (kb * 32 + l32) * (DH + 8) + 16 * s + 8 * half), qf[s], st);
-        dp = mfma32(ld_frag(sV + (kb * 32 + l32) * (DH + 8) + 16 * s + 8 * half), df[s], dp);
+        st = mfma32(rd.frag(sK, kb, s), qf[s], st);
+        dp = mfma32(rd.frag(sV, kb, s), df[s], dp);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int key = kt * KT + kb * 32 + perm_pos(r, half);
+        const int key = k0 + perm_pos(r, half);
         const bool ok = full || (qv && key < S && (!CAUSAL || key <= q));
         const float p = ok ? __builtin_amdgcn_exp2f(fmaf(st[r], sl2, -lse)) : 0.f;
         st[r] = p * (dp[r] - dsum);  // dS
@@ -350,23 +379,25 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
       for (int j = 0; j < 2; ++j) {
         const bf16x8 sf = pack8(st, j);
 #pragma unroll
-        for (int db = 0; db < DH / 32; ++db)
-          dq[db] = mfma32(perm_frag<DH>(sK, db, kb, j, lane), sf, dq[db]);
+        for (int db = 0; db < DH / 32; ++db) dq[db] = mfma32(rd.perm(sK, db, kb, j), sf, dq[db]);
       }
     }
   }
-  if (qv) {
-    bf16* dst = static_cast<bf16*>(a.dqkv) + (long)(b * S + q) * a.ld_dqkv + hd * DH;
-    store_rows<DH>(dq, scale, a.rope, q, rtab, half, dst);
-  }
+  tiles_ready();  // the tiles' space now takes the dQ rows
+  if (q0 >= S) return;
+  if (a.rope) unrotate<DH>(dq, min(q, S - 1), a.rope_tab, half);
+  store_rows_staged<DH>(dq, scale, half, lane, sm + wave * 32 * (DH + 8),
+                        static_cast<bf16*>(a.dqkv) + (long)(b * S + q0) * a.ld_dqkv + hd * DH, a.ld_dqkv,
+                        stream_out(3l * a.B * S * a.H * DH * 2), S - q0);
 }
 
 // dK/dV pass (lane = key)
-template <int DH, bool CAUSAL, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 64 ? 2 : 1))) void attn_bwd_dkdv_bf16(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16 sQ[KT * (DH + 8)];
-  __shared__ __attribute__((aligned(16))) bf16 sO[KT * (DH + 8)];
-  __shared__ float sL[KT], sD[KT];
+template <int DH, bool CAUSAL, int NW, int KR>
+__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_bf16(AttnArgs a) {
+  constexpr int TILE = KR * DH;
+  __shared__ __attribute__((aligned(1024))) bf16 sm[4 * TILE];  // [buffer][Q, dO]
+  __shared__ __attribute__((aligned(16))) float sL[2][KR], sD[2][KR];
+  static_assert(4 * TILE >= NW * 32 * (DH + 8) && KR <= 64 * NW, "the dK / dV rows fit the tiles' space");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
   int kb0, bh;
   if (CAUSAL) {
@@ -377,18 +408,42 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
     bh = blk / gridDim.x;
   }
   const int b = bh / a.H, hd = bh % a.H, S = a.S;
-  const int key = kb0 * (32 * NW) + wave * 32 + l32;
+  const int k0 = kb0 * (32 * NW) + wave * 32, key = k0 + l32;  // this wave's first key, this lane's
   const bool kv = key < S;
   const int d = a.H * DH;
-  const float2* rtab = a.rope_tab;
   const float scale = rsqrtf((float)DH), sl2 = kLog2e * scale;
   const bf16* qkv = static_cast<const bf16*>(a.qkv);
-  const bf16* dO = static_cast<const bf16*>(a.dout);
   const long krow = (long)(b * S + (kv ? key : 0));
-
+  const TileRead<DH> rd(lane);
+  const int nqt = (S + KR - 1) / KR, qt0 = CAUSAL ? (kb0 * (32 * NW)) / KR : 0;
+  auto issue = [&](int qt) {
+    bf16* dst = sm + (qt & 1) * 2 * TILE;
+    tile_dma<DH, KR, NW>(qkv, a.ld_qkv, hd * a.qkv_hs, b, S, qt * KR, dst);
+    tile_dma<DH, KR, NW>(static_cast<const bf16*>(a.dout), a.ld_do, hd * DH, b, S, qt * KR, dst + TILE);
+  };
+  // the row statistics of tile qt, one query per thread of the first KR (rows past S: 0)
+  auto load_stats = [&](int qt, float& lv, float& dv) {
+    const int qq = qt * KR + (int)threadIdx.x;
+    const long qi = (long)bh * S + min(qq, S - 1);
+    lv = dv = 0.f;
+    if (threadIdx.x < KR) {
+      lv = a.lse[qi];
+      dv = a.dsum[qi];
+      if (qq >= S) lv = dv = 0.f;
+    }
+  };
+  auto put_stats = [&](int qt, float lv, float dv) {
+    if (threadIdx.x < KR) {
+      sL[qt & 1][threadIdx.x] = lv;
+      sD[qt & 1][threadIdx.x] = dv;
+    }
+  };
+  issue(qt0);
+  float lnext, dnext;
+  load_stats(qt0, lnext, dnext);
   bf16x8 kf[DH / 16], vf[DH / 16];
-  load_row_frags<DH>(qkv + krow * a.ld_qkv + a.qkv_ko + hd * a.qkv_hs, key, kv, rot_load(a), rtab, half, kf);
-  load_row_frags<DH>(qkv + krow * a.ld_qkv + a.qkv_vo + hd * a.qkv_hs, key, kv, false, nullptr, half, vf);
+  load_row_frags<DH>(qkv + krow * a.ld_qkv + a.qkv_ko + hd * a.qkv_hs, kv, half, kf);
+  load_row_frags<DH>(qkv + krow * a.ld_qkv + a.qkv_vo + hd * a.qkv_hs, kv, half, vf);
 
   f32x16 dk[DH / 32], dv[DH / 32];
 #pragma unroll
@@ -396,70 +451,66 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
 #pragma unroll
     for (int r = 0; r < 16; ++r) dk[i][r] = dv[i][r] = 0.f;
 
-  const int nqt = (S + KT - 1) / KT;
-  const int qt0 = CAUSAL ? (kb0 * (32 * NW)) / KT : 0;
-  // the next Q/dO tile's global loads are in flight while the current one is used
-  TileLoad<DH, 64 * NW> tq, tdo;
-  if (qt0 < nqt) {
-    tq.issue(qkv, a.ld_qkv, hd * a.qkv_hs, b, S, qt0 * KT);
-    tdo.issue(dO, a.ld_do, hd * DH, b, S, qt0 * KT);
-  }
+  put_stats(qt0, lnext, dnext);
   for (int qt = qt0; qt < nqt; ++qt) {
-    // every key of the workgroup and every query of the tile in range, no causal mask
-    const bool full = !CAUSAL && (kb0 + 1) * (32 * NW) <= S && (qt + 1) * KT <= S;
-    __syncthreads();
-    tq.store(sQ, rot_load(a), S, qt * KT, rtab);
-    tdo.store(sO, false, S, qt * KT, rtab);
-    for (int i = threadIdx.x; i < KT; i += blockDim.x) {
-      const int qq = qt * KT + i;
-      const long qi = (long)bh * S + min(qq, S - 1);
-      const float lv = a.lse[qi], dv = a.dsum[qi];
-      sL[i] = qq < S ? lv : 0.f;
-      sD[i] = qq < S ? dv : 0.f;
-    }
-    // issued after the row statistics: loads complete in order, so waiting
-    // for those must not wait for the prefetch
+    tiles_ready();
     if (qt + 1 < nqt) {
-      tq.issue(qkv, a.ld_qkv, hd * a.qkv_hs, b, S, (qt + 1) * KT);
-      tdo.issue(dO, a.ld_do, hd * DH, b, S, (qt + 1) * KT);
+      load_stats(qt + 1, lnext, dnext);
+      issue(qt + 1);
     }
-    __syncthreads();
+    const bf16* sQ = sm + (qt & 1) * 2 * TILE;
+    const bf16* sO = sQ + TILE;
+    const float* pL = sL[qt & 1];
+    const float* pD = sD[qt & 1];
     // one query block at a time (not unrolled), as in the dQ pass
 #pragma unroll 1
-    for (int qb = 0; qb < KT / 32; ++qb) {
+    for (int qb = 0; qb < KR / 32; ++qb) {
+      const int q0 = qt * KR + qb * 32;
+      if (k0 >= S || q0 >= S) break;          // wave-uniform
+      if (CAUSAL && q0 + 31 < k0) continue;
+      const bool full = k0 + 32 <= S && q0 + 32 <= S && (!CAUSAL || k0 + 31 <= q0);
       f32x16 st, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) st[r] = dp[r] = 0.f;
 #pragma unroll
       for (int s = 0; s < DH / 16; ++s) {
-        st = mfma32(ld_frag(sQ + (qb * 32 + l32) * (DH + 8) + 16 * s + 8 * half), kf[s], st);
-        dp = mfma32(ld_frag(sO + (qb * 32 + l32) * (DH + 8) + 16 * s + 8 * half), vf[s], dp);
+        st = mfma32(rd.frag(sQ, qb, s), kf[s], st);
+        dp = mfma32(rd.frag(sO, qb, s), vf[s], dp);
       }
-      f32x16 ds;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int qi = qb * 32 + perm_pos(r, half), qq = qt * KT + qi;
-        const bool ok = full || (kv && qq < S && (!CAUSAL || key <= qq));
-        const float p = ok ? __builtin_amdgcn_exp2f(fmaf(st[r], sl2, -sL[qi])) : 0.f;
-        st[r] = p;
-        ds[r] = p * (dp[r] - sD[qi]);
+      for (int g = 0; g < 4; ++g) {  // queries q0 + 8g + 4*half + 0..3
+        const float4 L = *reinterpret_cast<const float4*>(pL + qb * 32 + 8 * g + 4 * half);
+        const float4 D = *reinterpret_cast<const float4*>(pD + qb * 32 + 8 * g + 4 * half);
+        const float lv[4] = {L.x, L.y, L.z, L.w}, sv[4] = {D.x, D.y, D.z, D.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = 4 * g + e, qq = q0 + 8 * g + 4 * half + e;
+          const bool ok = full || (kv && qq < S && (!CAUSAL || key <= qq));
+          const float p = ok ? __builtin_amdgcn_exp2f(fmaf(st[r], sl2, -lv[e])) : 0.f;
+          st[r] = p;
+          dp[r] = p * (dp[r] - sv[e]);  // dS
+        }
       }
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const bf16x8 pf = pack8(st, j), sf = pack8(ds, j);
+        const bf16x8 pf = pack8(st, j), sf = pack8(dp, j);
 #pragma unroll
         for (int db = 0; db < DH / 32; ++db) {
-          dv[db] = mfma32(perm_frag<DH>(sO, db, qb, j, lane), pf, dv[db]);
-          dk[db] = mfma32(perm_frag<DH>(sQ, db, qb, j, lane), sf, dk[db]);
+          dv[db] = mfma32(rd.perm(sO, db, qb, j), pf, dv[db]);
+          dk[db] = mfma32(rd.perm(sQ, db, qb, j), sf, dk[db]);
         }
       }
     }
+    if (qt + 1 < nqt) put_stats(qt + 1, lnext, dnext);  // the other buffer: last read before this tile's barrier
   }
-  if (kv) {
-    bf16* dst = static_cast<bf16*>(a.dqkv) + (long)(b * S + key) * a.ld_dqkv;
-    store_rows<DH>(dk, scale, a.rope, key, rtab, half, dst + d + hd * DH);
-    store_rows<DH>(dv, 1.f, false, key, nullptr, half, dst + 2 * d + hd * DH);
-  }
+  tiles_ready();  // the tiles' space now takes the dK, then the dV rows
+  if (k0 >= S) return;
+  if (a.rope) unrotate<DH>(dk, min(key, S - 1), a.rope_tab, half);
+  bf16* dst = static_cast<bf16*>(a.dqkv) + (long)(b * S + k0) * a.ld_dqkv + d + hd * DH;
+  bf16* stage = sm + wave * 32 * (DH + 8);
+  const bool nt = stream_out(3l * a.B * S * d * 2);
+  store_rows_staged<DH>(dk, scale, half, lane, stage, dst, a.ld_dqkv, nt, S - k0);
+  store_rows_staged<DH>(dv, 1.f, half, lane, stage, dst + d, a.ld_dqkv, nt, S - k0);
 }
 
 // Whole backward of one (batch, head) with S <= KT (one query block, one key
@@ -867,12 +918,13 @@ static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) 
 
 // four waves (128 queries or keys) per workgroup
 constexpr int ATT_NW = 4;
+constexpr int ATT_KR = 64;  // rows of the other side per tile
 
 template <int DH>
 static hipError_t fwd_dh(const AttnArgs& a, hipStream_t s) {
   dim3 grid((a.S + 32 * ATT_NW - 1) / (32 * ATT_NW), a.B * a.H), block(64 * ATT_NW);
-  if (a.causal) RG_LAUNCH((attn_fwd_bf16<DH, true, ATT_NW>), grid, block, 0, s, a);
-  else RG_LAUNCH((attn_fwd_bf16<DH, false, ATT_NW>), grid, block, 0, s, a);
+  if (a.causal) RG_LAUNCH((attn_fwd_bf16<DH, true, ATT_NW, ATT_KR>), grid, block, 0, s, a);
+  else RG_LAUNCH((attn_fwd_bf16<DH, false, ATT_NW, ATT_KR>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 template <int DH>
@@ -884,11 +936,11 @@ static hipError_t bwd_dh(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
   }
   if (a.causal) {
-    RG_LAUNCH((attn_bwd_dq_bf16<DH, true, ATT_NW>), grid, block, 0, s, a);
-    RG_LAUNCH((attn_bwd_dkdv_bf16<DH, true, ATT_NW>), grid, block, 0, s, a);
+    RG_LAUNCH((attn_bwd_dq_bf16<DH, true, ATT_NW, ATT_KR>), grid, block, 0, s, a);
+    RG_LAUNCH((attn_bwd_dkdv_bf16<DH, true, ATT_NW, ATT_KR>), grid, block, 0, s, a);
   } else {
-    RG_LAUNCH((attn_bwd_dq_bf16<DH, false, ATT_NW>), grid, block, 0, s, a);
-    RG_LAUNCH((attn_bwd_dkdv_bf16<DH, false, ATT_NW>), grid, block, 0, s, a);
+    RG_LAUNCH((attn_bwd_dq_bf16<DH, false, ATT_NW, ATT_KR>), grid, block, 0, s, a);
+    RG_LAUNCH((attn_bwd_dkdv_bf16<DH, false, ATT_NW, ATT_KR>), grid, block, 0, s, a);
   }
   return hipGetLastError();
 }
@@ -905,7 +957,7 @@ static hipError_t check(int dtype, const AttnArgs& a, bool bwd) {
   if (dtype == DT_BF16) {
     if (a.dh != 64 && a.dh != 128) return hipErrorInvalidValue;
     if (a.ld_qkv % 8 || a.ld_o % 8 || !al16(a.qkv) || !al16(a.o)) return hipErrorInvalidValue;
-    if (bwd && (a.ld_do % 8 || a.ld_dqkv % 4 || !al16(a.dout))) return hipErrorInvalidValue;
+    if (bwd && (a.ld_do % 8 || a.ld_dqkv % 8 || !al16(a.dout) || !al16(a.dqkv))) return hipErrorInvalidValue;
   } else {
     if (a.dh > 128 || a.dh % 2 || a.S > 4096 || a.causal || a.rope) return hipErrorInvalidValue;
   }
