@@ -171,17 +171,18 @@ constexpr int epi_rows(int bm, int row_bytes, int lds_bytes) {
   return r;
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NS, Epi E, int GROUP = 4>
+template <int BM, int BN, int WM, int WN, int KG, int BK, int NS, Epi E, int GROUP = 4>
 __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
-  constexpr int NW = WM * WN, NT = 64 * NW;
+  constexpr int NW = WM * WN * KG, NT = 64 * NW;
   constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
   constexpr int ROWB = BK * 2, CPR = BK / 8, RPI = 64 / CPR, SWD = 16 / CPR;
   constexpr int LA = BM / (RPI * NW), LB = BN / (RPI * NW), LPT = LA + LB;
-  constexpr int KS = BK / 16;
+  constexpr int KS = BK / 16 / KG;  // k-steps per tile and wave
   constexpr int STAGE = (BM + BN) * ROWB;
   static_assert(LA * RPI * NW == BM && LB * RPI * NW == BN, "DMA rows must tile the block");
   static_assert(FM * 32 * WM == BM && FN * 32 * WN == BN, "wave tiles of 32x32 blocks");
-  static_assert(KS % 2 == 0, "even number of k-steps per tile");
+  static_assert(KS % 2 == 0, "even number of k-steps per tile and wave");
+  static_assert(KG == 1 || E != Epi::Attn, "the attention epilogue takes whole sums");
   static_assert(NS >= 2 && NS <= 4 && LPT * (NS - 1) < 64, "stages / vmcnt range");
   static_assert(E != Epi::SwiGlu || FN % 2 == 0, "SwiGlu needs gate/up block pairs");
   // output tile staging for the epilogue: fp32 rows of BN + 4 (the 16-B pad
@@ -192,9 +193,11 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
   constexpr bool HAS_BIAS = E == Epi::Store || E == Epi::Gelu || E == Epi::Attn;
   constexpr int BIASB = HAS_BIAS ? BN * 4 : 0;
   // (256x256 blocks take 3 KB more than their stages: two passes instead of four)
-  constexpr int EPI_LDS = BM == 256 && BN == 256 ? 128 * CPF * 4 + BIASB : NS * STAGE;
-  constexpr int RPP = epi_rows(BM, CPF * 4, EPI_LDS - BIASB);
-  static_assert(RPP >= 32 && BM % RPP == 0 && RPP * CPF * 4 + BIASB <= EPI_LDS,
+  // and each of the KG k-groups has its own copy of the rows
+  constexpr int EPI_MIN = (BM == 256 && BN == 256 ? 128 : 64) * KG * CPF * 4 + BIASB;
+  constexpr int EPI_LDS = EPI_MIN > NS * STAGE ? EPI_MIN : NS * STAGE;
+  constexpr int RPP = epi_rows(BM, KG * CPF * 4, EPI_LDS - BIASB);
+  static_assert(RPP >= 32 && BM % RPP == 0 && KG * RPP * CPF * 4 + BIASB <= EPI_LDS && EPI_LDS <= 160 * 1024,
                 "epilogue passes of whole 32-row blocks");
   constexpr int LDS = EPI_LDS > NS * STAGE ? EPI_LDS : NS * STAGE;
   // the DMA is invisible to the compiler, so one array serves every stage
@@ -202,7 +205,7 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
   auto stage_base = [&](auto S) -> char* { return smem + decltype(S)::value * STAGE; };
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int kg = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
   int m0, n0;
   tile_coords<BM, BN, GROUP>(a.M, a.N, m0, n0);
   const bf16* A = static_cast<const bf16*>(a.A);
@@ -277,7 +280,7 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
   const int l32 = lane & 31, half = lane >> 5, sw = (l32 / SWD) % CPR;
   bf16x8 fa[2][FM], fb[2][FN];
   auto read_frags = [&](const char* base, int ks, int slot) {
-    const int off = 16 * ((2 * ks + half) ^ sw);
+    const int off = 16 * ((2 * (ks * KG + kg) + half) ^ sw);
     const char* sa = base + (wm * TM + l32) * ROWB + off;
     const char* sb = base + (BM + wn * TN + l32) * ROWB + off;
 #pragma unroll
@@ -419,19 +422,27 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
     const float4 hi = *reinterpret_cast<const float4*>(cf + row * CPF + col + 4);
     v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
     v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+#pragma unroll
+    for (int k = 1; k < KG; ++k) {  // the k-groups' sums, in order
+      const float4 l = *reinterpret_cast<const float4*>(cf + (k * RPP + row) * CPF + col);
+      const float4 h = *reinterpret_cast<const float4*>(cf + (k * RPP + row) * CPF + col + 4);
+      v[0] += l.x; v[1] += l.y; v[2] += l.z; v[3] += l.w;
+      v[4] += h.x; v[5] += h.y; v[6] += h.z; v[7] += h.w;
+    }
   };
   constexpr int CPRW8 = BN / 8, NCH8 = RPP * CPRW8;
 #pragma unroll
   for (int p = 0; p < BM / RPP; ++p) {
     // this pass's second-operand chunks, all loads in flight before the
     // staging so that their latency overlaps it
-    bf16x8 ax[HAS_AUX ? NCH8 / NT : 1][PF_SEG];
+    constexpr int NCI = (NCH8 + NT - 1) / NT;
+    bf16x8 ax[HAS_AUX ? NCI : 1][PF_SEG];
     if constexpr (HAS_AUX) {
 #pragma unroll
-      for (int i = 0; i < NCH8 / NT; ++i) {
+      for (int i = 0; i < NCI; ++i) {
         const int idx = tid + i * NT;
         const int m = m0 + p * RPP + idx / CPRW8, n = n0 + (idx % CPRW8) * 8;
-        if (m < M && n < N) {
+        if ((NCH8 % NT == 0 || idx < NCH8) && m < M && n < N) {
           const bf16* x = static_cast<const bf16*>(a.aux) + (long)m * a.ld_aux + n;
 #pragma unroll
           for (int sg = 0; sg < PF_SEG; ++sg) ax[i][sg] = *reinterpret_cast<const bf16x8*>(x + sg * a.half);
@@ -446,7 +457,7 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int row = wm * TM + i * 32 + l32 - p * RPP, col = wn * TN + j * 32 + 8 * g + 4 * half;
-          *reinterpret_cast<float4*>(cf + row * CPF + col) =
+          *reinterpret_cast<float4*>(cf + (kg * RPP + row) * CPF + col) =
               make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
         }
     }
@@ -497,19 +508,17 @@ __device__ __forceinline__ void gemm_bf16_pipe_body(const GemmArgs& a) {
         st8(out + (long)m * a.ldo + n2, v2, a.nt);
       }
     } else if constexpr (HAS_AUX) {
-      static_assert(NCH8 % NT == 0, "whole passes");
 #pragma unroll
-      for (int i = 0; i < NCH8 / NT; ++i) {
+      for (int i = 0; i < NCI; ++i) {
         const int idx = tid + i * NT;
         const int row = idx / CPRW8, c = (idx % CPRW8) * 8;
         const int m = m0 + p * RPP + row, n = n0 + c;
-        if (m >= M || n >= N) continue;
+        if ((NCH8 % NT != 0 && idx >= NCH8) || m >= M || n >= N) continue;
         float v[8];
         ld_tile8(row, c, v);
         epilogue8<E>(a, m, n, v, cbias + c, ax[i]);
       }
     } else {
-      static_assert(NCH8 % NT == 0, "whole passes");
 #pragma unroll 2
       for (int idx = tid; idx < NCH8; idx += NT) {
         const int row = idx / CPRW8, c = (idx % CPRW8) * 8;
@@ -640,10 +649,10 @@ __device__ __forceinline__ void gemm_f32_body(const GemmArgs& a) {
 // Two-stage 4-wave tiles run two workgroups per CU (LDS <= 80 KB), so their
 // registers must fit two waves per SIMD; the bound says so to the compiler.
 #define RG_GEMM_KERNELS(NAME)                                                        \
-  template <int BM, int BN, int WM, int WN, int BK, int NS, Epi E>                   \
-  __global__ __launch_bounds__(64 * WM * WN, NS == 2 && WM * WN == 4 ? 2 : 1) void   \
+  template <int BM, int BN, int WM, int WN, int KG, int BK, int NS, Epi E>           \
+  __global__ __launch_bounds__(64 * WM * WN * KG, NS == 2 && WM * WN * KG == 4 ? 2 : 1) void \
   NAME##_pipe(GemmArgs a) {                                                          \
-    gemm_bf16_pipe_body<BM, BN, WM, WN, BK, NS, E, 4>(a);                            \
+    gemm_bf16_pipe_body<BM, BN, WM, WN, KG, BK, NS, E, 4>(a);                        \
   }                                                                                  \
   template <Epi E, int R>                                                            \
   __global__ __launch_bounds__(256) void NAME##_f32(GemmArgs a) {                    \
@@ -692,16 +701,21 @@ static constexpr bool role_has(Role r, Epi e) {
 //   128x96   4096 x 768 x 3072    27.6 (128x128 31.6)
 //   64x128   1827 x 768 x 3072    20.8 (128x96 26.2)
 //   64x64    256 x 4096 x 4096    20.4 (64x128 27.2)
-//   64x32    100 x 4096 x 11008   38.6 (64x64 46.5)
+//   32x64    100 x 4096 x 11008   34.4 (32x32 38.6, 64x64 46.2)
+//   32x32    37 x 768 x 3072       8.0 (32x64 10.3, 64x64 13.7)
+// The last two are one wave wide and deal K to four wave groups (KG): the whole
+// tile from fragments read once, and four waves' loads in flight.  On larger
+// tiles KG brought nothing (128x96 27.6 -> 28.6).
 // slots: workgroups the chip holds.  Where that is 512 (two per CU), (f, r) are those of
 // a full round and (f1, r1) those of one with at most a workgroup per CU.
 enum Cfg {
-  C_64x32, C_64x64, C_64x128, C_64x128_K64, C_128x96, C_128x128, C_128x128_2, C_128x192, C_128x192_2,
+  C_32x32, C_32x64, C_64x64, C_64x128, C_64x128_K64, C_128x96, C_128x128, C_128x128_2, C_128x192, C_128x192_2,
   C_256x128, C_256x192, C_256x256, N_CFGS
 };
 struct Tile { int bm, bn, bk, slots; float f, r, f1, r1; };
 static constexpr Tile TILE[N_CFGS] = {
-    {64, 32, 128, 256, 2.0f, .21f, 0, 0},      {64, 64, 128, 256, 2.5f, .27f, 0, 0},
+    {32, 32, 128, 512, 2.8f, .21f, 2.8f, .11f}, {32, 64, 128, 256, 1.8f, .19f, 0, 0},
+    {64, 64, 128, 256, 2.5f, .27f, 0, 0},
     {64, 128, 128, 256, 2.2f, .40f, 0, 0},     {64, 128, 64, 256, 2.3f, .43f, 0, 0},
     {128, 96, 64, 256, 3.9f, .49f, 0, 0},      {128, 128, 64, 256, 3.3f, .56f, 0, 0},
     {128, 128, 64, 512, 4.5f, .96f, 3.0f, .8f}, {128, 192, 64, 256, 4.6f, .73f, 0, 0},
@@ -724,7 +738,11 @@ static Cfg choose_tile(Epi E, int M, int N, int K) {
     const Tile& t = TILE[c];
     if (!cfg_has(E, (Cfg)c) || K % t.bk) continue;
     const long n = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), full = n / t.slots, rem = n % t.slots;
-    const double k = K / 64, round = t.f + t.r * k;
+    // dSwiGLU moves 6 B more per output than the others, which a tile alone on its CU does
+    // not hide (about 20 GB/s a CU): 2048 x 11008 x 4096 on 256x192 was 17 us slower than
+    // on 128x192, two per CU
+    const double epi = E == Epi::DSwiGlu && t.slots == 256 ? t.bm * t.bn * 6 / 20e3 : 0.;
+    const double k = K / 64, round = t.f + epi + t.r * k;
     const double us = full * round + (rem == 0 ? 0. : (t.slots > 256 && rem <= 256) ? t.f1 + t.r1 * k : round);
     if (us < least) { least = us; best = (Cfg)c; }
   }
@@ -744,7 +762,7 @@ static hipError_t launch_role(Cfg cfg, int dtype, const GemmArgs& a, hipStream_t
   } else {
     const dim3 block(256);
     if constexpr (E == Epi::Attn) {  // bf16, 128x192 tiles only (checked by the caller)
-      RG_LAUNCH((gemm_qkv_fwd_pipe<128, 192, 2, 2, 64, 2, Epi::Attn>), dim3((a.N / 192) * (a.M / 128)), block, 0, s, a);
+      RG_LAUNCH((gemm_qkv_fwd_pipe<128, 192, 2, 2, 1, 64, 2, Epi::Attn>), dim3((a.N / 192) * (a.M / 128)), block, 0, s, a);
       return hipGetLastError();
     } else {
     if (dtype == DT_F32) {
@@ -770,28 +788,29 @@ static hipError_t launch_role(Cfg cfg, int dtype, const GemmArgs& a, hipStream_t
         return hipGetLastError();
       }
     }
-#define RG_CASE(C, NAME, WM, WN, NS)                                                          \
+#define RG_CASE(C, NAME, WM, WN, KG, NS)                                                          \
     case C:                                                                                  \
       if constexpr (cfg_has(E, C))                                                           \
-        RG_LAUNCH((NAME##_pipe<TILE[C].bm, TILE[C].bn, WM, WN, TILE[C].bk, NS, E>),          \
+        RG_LAUNCH((NAME##_pipe<TILE[C].bm, TILE[C].bn, WM, WN, KG, TILE[C].bk, NS, E>),          \
                   dim3(((a.N + TILE[C].bn - 1) / TILE[C].bn) * ((a.M + TILE[C].bm - 1) / TILE[C].bm)), \
-                  dim3(64 * WM * WN), 0, s, a);                                              \
+                  dim3(64 * WM * WN * KG), 0, s, a);                                              \
       else return hipErrorInvalidValue;                                                      \
       break;
 #define RG_LAUNCH_CFG(NAME)                      \
   switch (cfg) {                                 \
-    RG_CASE(C_64x32, NAME, 2, 1, 4)              \
-    RG_CASE(C_64x64, NAME, 2, 2, 3)              \
-    RG_CASE(C_64x128, NAME, 2, 2, 3)             \
-    RG_CASE(C_64x128_K64, NAME, 2, 2, 4)         \
-    RG_CASE(C_128x96, NAME, 4, 1, 4)             \
-    RG_CASE(C_128x128, NAME, 2, 2, 3)            \
-    RG_CASE(C_128x128_2, NAME, 2, 2, 2)          \
-    RG_CASE(C_128x192, NAME, 2, 2, 4)            \
-    RG_CASE(C_128x192_2, NAME, 2, 2, 2)          \
-    RG_CASE(C_256x128, NAME, 4, 2, 3)            \
-    RG_CASE(C_256x192, NAME, 4, 2, 2)            \
-    RG_CASE(C_256x256, NAME, 4, 2, 2)            \
+    RG_CASE(C_32x32, NAME, 1, 1, 4, 4)           \
+    RG_CASE(C_32x64, NAME, 1, 1, 4, 4)           \
+    RG_CASE(C_64x64, NAME, 2, 2, 1, 3)              \
+    RG_CASE(C_64x128, NAME, 2, 2, 1, 3)             \
+    RG_CASE(C_64x128_K64, NAME, 2, 2, 1, 4)         \
+    RG_CASE(C_128x96, NAME, 4, 1, 1, 4)             \
+    RG_CASE(C_128x128, NAME, 2, 2, 1, 3)            \
+    RG_CASE(C_128x128_2, NAME, 2, 2, 1, 2)          \
+    RG_CASE(C_128x192, NAME, 2, 2, 1, 4)            \
+    RG_CASE(C_128x192_2, NAME, 2, 2, 1, 2)          \
+    RG_CASE(C_256x128, NAME, 4, 2, 1, 3)            \
+    RG_CASE(C_256x192, NAME, 4, 2, 1, 2)            \
+    RG_CASE(C_256x256, NAME, 4, 2, 1, 2)            \
     default: return hipErrorInvalidValue;        \
   }
     // only R's kernels are instantiated

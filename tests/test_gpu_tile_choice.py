@@ -1,5 +1,5 @@
 """Parity of the tiles that the projection GEMMs take by estimated time: the
-small ones (64x32, 64x64, 64x128 with 128- and 64-wide k-tiles), the four-stage
+small ones (32x32, 32x64, 64x64, 64x128 with 128- and 64-wide k-tiles), the four-stage
 128x192 and the 256x256, each with ragged last tiles where its range has them.
 Method and bounds are those of the tile cases in test_gpu_tiles (which compares
 three different sequences: batches of three or more)."""
@@ -11,8 +11,10 @@ from test_gpu_tiles import torch  # noqa: F401  (the fixture)
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    # 64x32 in every projection, 25 of 64 rows past the end
+    # 32x32 and 32x64 with K dealt to four wave groups, 25 rows past the end
     "choice_bert_t39": ("bert", 768, 12, 3072, 13, 3, 2401),
+    # 32x64 with store, GELU, residual and GELU' epilogues
+    "choice_bert_t90": ("bert", 1024, 16, 4096, 30, 3, 2408),
     # 64x64, and 64x128 with 64-wide k-tiles (K = 960 is no multiple of 128)
     "choice_bert_t300": ("bert", 1024, 16, 960, 100, 3, 2402),
     # 64x128 in the rotary and SwiGLU epilogues, 29 of 64 rows past the end
