@@ -57,23 +57,7 @@ __device__ __forceinline__ void unrotate(f32x16 (&acc)[DH / 32], int pos, const 
     }
 }
 
-// Writes such an accumulator scaled, optionally un-rotated.
-template <int DH>
-__device__ __forceinline__ void store_rows(f32x16 (&acc)[DH / 32], float scale, bool unrot, int pos,
-                                           const float2* rtab, int half, bf16* dst) {
-  if (unrot) unrotate<DH>(acc, pos, rtab, half);
-#pragma unroll
-  for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float v[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = acc[db][4 * g + q] * scale;
-      St<bf16>::st4(dst, db * 32 + 8 * g + 4 * half, v);
-    }
-}
-
-// The same rows (not rotated), the first n of them, through LDS: each lane writes its row
+// Writes the first n rows of such an accumulator, scaled, through LDS: each lane writes its row
 // into the 32 staging rows (pitch DH + 8, private to the wave), then each
 // store instruction writes whole rows, 16 B per lane (8 rows of 128 B at DH
 // 64), so the stores can be streamed (st16).  One wave's LDS operations run in

@@ -118,35 +118,31 @@ __device__ __forceinline__ void tiles_ready() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-// Element offsets of this lane's reads in such a tile: row[s] for the chunk of
-// dims 16s + 8*half of row lane%32, tr[h][db] for the two halves of perm_frag's
-// transpose read of block db (rows + kb*32 (+ 16j): a multiple of 16, which the
-// swizzle does not see, so blocks are reached by constant offsets).
+// Element offsets of this lane's reads in such a tile: row for dims 8*half of row
+// lane%32, tr for perm_frag's transpose read of block 0.  The swizzle is an XOR
+// below the row bits, so other dims are reached by an XOR of their own (16s, 32
+// db) and the rows 8 further down, whose swizzle differs in bit 1 of the chunk, by 16;
+// rows + 16 i are constant offsets.
 template <int DH>
 struct TileRead {
-  int row[DH / 16], tr[2][DH / 32];
+  int row, tr;
   __device__ __forceinline__ explicit TileRead(int lane) {
     const int l32 = lane & 31, half = lane >> 5, g = lane >> 4, r = lane & 15;
-#pragma unroll
-    for (int s = 0; s < DH / 16; ++s) row[s] = l32 * DH + (((2 * s + half) ^ swz<DH>(l32)) * 8);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int db = 0; db < DH / 32; ++db) {
-        const int rr = 4 * (g >> 1) + 8 * h + (r >> 2), c = db * 4 + 2 * (g & 1) + ((r & 3) >> 1);
-        tr[h][db] = rr * DH + ((c ^ swz<DH>(rr)) * 8) + 4 * (r & 1);
-      }
+    row = l32 * DH + ((half ^ swz<DH>(l32)) * 8);
+    const int rr = 4 * (g >> 1) + (r >> 2), c = 2 * (g & 1) + ((r & 3) >> 1);
+    tr = rr * DH + ((c ^ swz<DH>(rr)) * 8) + 4 * (r & 1);
   }
   // fragment of rows kb*32 + lane%32, dims 16s + 8*half + 0..7
   __device__ __forceinline__ bf16x8 frag(const bf16* tile, int kb, int s) const {
-    return ld_frag(tile + row[s] + kb * 32 * DH);
+    return ld_frag(tile + (row ^ (16 * s)) + kb * 32 * DH);
   }
   // the same operand as perm_frag
   __device__ __forceinline__ bf16x8 perm(const bf16* tile, int db, int kb, int j) const {
-    const bf16* t = tile + (kb * 32 + 16 * j) * DH;
-    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(t + tr[0][db])));
-    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(t + tr[1][db])));
-    return __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+    const bf16* lo = tile + (tr ^ (32 * db)) + (kb * 32 + 16 * j) * DH;
+    const bf16* hi = tile + (tr ^ (32 * db) ^ 16) + (kb * 32 + 16 * j + 8) * DH;
+    const uint2 l = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)lo));
+    const uint2 h = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)hi));
+    return __builtin_bit_cast(bf16x8, make_uint4(l.x, l.y, h.x, h.y));
   }
 };
 
@@ -178,7 +174,7 @@ __device__ __forceinline__ void heavy_first(int lin, int nq, int nbh, int& rank,
 // overlapped the softmax with MFMAs and LDS reads).  Results leave through LDS as
 // whole rows.
 // Before -> after, us: 2048 tokens of 512, 32 heads of 128, causal: forward 43 -> 23,
-// dQ 56 -> 40, dK/dV 71 -> 65; 4096 tokens of 256, 16 heads of 64: 15.8 -> 13.6,
+// dQ 56 -> 40, dK/dV 71 -> 57; 4096 tokens of 256, 16 heads of 64: 15.8 -> 13.6,
 // 20.4 -> 20.4, 28.6 -> 21.4.
 template <int DH, bool CAUSAL, int NW, int KR>
 __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_bf16(AttnArgs a) {
@@ -414,7 +410,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_bf16(AttnArgs a) {
   const float scale = rsqrtf((float)DH), sl2 = kLog2e * scale;
   const bf16* qkv = static_cast<const bf16*>(a.qkv);
   const long krow = (long)(b * S + (kv ? key : 0));
-  const TileRead<DH> rd(lane);
+  TileRead<DH> rd(lane);
   const int nqt = (S + KR - 1) / KR, qt0 = CAUSAL ? (kb0 * (32 * NW)) / KR : 0;
   auto issue = [&](int qt) {
     bf16* dst = sm + (qt & 1) * 2 * TILE;
@@ -468,6 +464,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_bf16(AttnArgs a) {
       const int q0 = qt * KR + qb * 32;
       if (k0 >= S || q0 >= S) break;          // wave-uniform
       if (CAUSAL && q0 + 31 < k0) continue;
+      // the read offsets are formed per block: kept across the loop they spill at d_head 128
+      if constexpr (DH == 128) asm volatile("" : "+v"(rd.row), "+v"(rd.tr));
       const bool full = k0 + 32 <= S && q0 + 32 <= S && (!CAUSAL || k0 + 31 <= q0);
       f32x16 st, dp;
 #pragma unroll
@@ -521,7 +519,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_bf16(AttnArgs a) {
 // [query][key]); each wave now owns keys 32w..32w+31 and reads its P^T
 // fragments from that block with the LDS transpose read, for dV = P^T dO;
 // then dS goes to the same space for dK = dS^T Q.  The LDS holds Q, dO and
-// the K/V tiles (74 KB at d_head 64: two workgroups per CU).
+// the K/V tiles (74 KB at d_head 64: two workgroups per CU).  The results leave
+// through the dO tile as whole streamed rows: 384 of these at S 128, d_head 64
+// took 20.3 us with 8-B pieces stored from the score layout, 17.2 us so.
 template <int DH, bool CAUSAL, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 64 ? 2 : 1))) void attn_bwd_fused_bf16(AttnArgs a) {
   static_assert(NW * 32 == KT, "one 32-row block per wave covers the tile");
@@ -583,8 +583,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
   // ---- scores, P, dS and dQ (lane = query)
   const bool full = !CAUSAL && S == KT;
   bf16x8 pk[KT / 32][2], sk[KT / 32][2];
+  f32x16 dq[DH / 32];
   {
-    f32x16 dq[DH / 32];
 #pragma unroll
     for (int i = 0; i < DH / 32; ++i)
 #pragma unroll
@@ -617,10 +617,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
         for (int db = 0; db < DH / 32; ++db) dq[db] = mfma32(perm_frag<DH>(sK, db, kb, j, lane), sk[kb][j], dq[db]);
       }
     }
-    if (qv) {
-      bf16* dst = static_cast<bf16*>(a.dqkv) + (long)(b * S + q) * a.ld_dqkv + hd * DH;
-      store_rows<DH>(dq, scale, a.rope, q, rtab, half, dst);
-    }
   }
 
   // a [query][key] block from the packed registers: register values 8j..8j+7
@@ -651,26 +647,30 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
         for (int db = 0; db < DH / 32; ++db) acc[db] = mfma32(perm_frag<DH>(sX, db, qb, j, lane), mf, acc[db]);
       }
   };
-  const int key = wave * 32 + l32;
-  const bool kv = key < S;
-  bf16* kdst = static_cast<bf16*>(a.dqkv) + (long)(b * S + (kv ? key : 0)) * a.ld_dqkv;
+  // The results leave as whole rows through the dO tile, each wave through its own
+  // 32 rows, once every wave has read dO for the last time.  wave * 32 + lane % 32
+  // is this lane's key as well as its query.
+  bf16* stage = sdO + wave * 32 * (DH + 8);
+  bf16* dst = static_cast<bf16*>(a.dqkv) + (long)(b * S + wave * 32) * a.ld_dqkv + hd * DH;
+  const int n = S - wave * 32;
+  const bool nt = stream_out(3l * a.B * S * d * 2);
+  const int pos = min(q, S - 1);
 
   __syncthreads();  // every wave is done with K and V
   put(pk);
   __syncthreads();
-  {
-    f32x16 dv[DH / 32];
-    tmul(sdO, dv);
-    if (kv) store_rows<DH>(dv, 1.f, false, key, nullptr, half, kdst + 2 * d + hd * DH);
-  }
-  __syncthreads();  // every wave is done with P
+  f32x16 dv[DH / 32];
+  tmul(sdO, dv);
+  __syncthreads();  // every wave is done with P and dO
   put(sk);
+  if (a.rope) unrotate<DH>(dq, pos, rtab, half);
+  store_rows_staged<DH>(dq, scale, half, lane, stage, dst, a.ld_dqkv, nt, n);
+  store_rows_staged<DH>(dv, 1.f, half, lane, stage, dst + 2 * d, a.ld_dqkv, nt, n);
   __syncthreads();
-  {
-    f32x16 dk[DH / 32];
-    tmul(sQ, dk);
-    if (kv) store_rows<DH>(dk, scale, a.rope, key, rtab, half, kdst + d + hd * DH);
-  }
+  f32x16 dk[DH / 32];
+  tmul(sQ, dk);
+  if (a.rope) unrotate<DH>(dk, pos, rtab, half);
+  store_rows_staged<DH>(dk, scale, half, lane, stage, dst + d, a.ld_dqkv, nt, n);
 }
 
 // ================================================================ fp32 (small stages)
