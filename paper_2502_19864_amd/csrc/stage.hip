@@ -153,8 +153,8 @@ static void plan_layout(const ringada_stage_desc& D, int B, int S, int c, Layout
   L.f2 = take(Td);
   const size_t fwd = cur;
   cur = 0;  // backward scratch
-  L.dact[0] = take(Td);
-  L.dact[1] = take(Td);
+  L.dact[0] = llama ? NONE : take(Td);  // pre-RMS blocks hand dX over in gdz
+  L.dact[1] = llama ? NONE : take(Td);
   L.df2 = take(Td);
   L.da1 = take(llama ? T2F : TF);
   L.dh1 = take(Td);
@@ -731,7 +731,7 @@ extern "C" ringada_status ringada_stage_forward(ringada_stage* st, void* stream,
 }
 
 // ================================================================ backward
-static ringada_status block_backward(const Ctx& c, int l, const void* G, void* dX, bool stop) {
+static ringada_status block_backward(const Ctx& c, int l, const void* G, void* dX, bool stop, bool copy_g) {
   ringada_stage* st = c.st;
   BlockBind& b = st->blocks[l];
   const Layout& L = st->L;
@@ -748,10 +748,11 @@ static ringada_status block_backward(const Ctx& c, int l, const void* G, void* d
   ab.wup = b.wk[1][2]; ab.wdn = b.wk[1][0]; ab.du = c.W(L.gdu[2 * l + 1]); ab.gu = c.W(L.ggu[2 * l + 1]);
   ab.dzin = stop_ffn ? nullptr : c.W(L.df2);
   ab.part = static_cast<float*>(c.W(L.adp));
-  // the gradient at the adapter output goes to this adapter's own buffer
-  // (pre-RMS: a copy of G, which a later block's dX overwrites)
-  ab.dz = c.W(L.gdz[2 * l + 1]);
-  const void* dz2 = ab.dz;
+  // the gradient at the adapter output, kept until the weight gradients: in this
+  // adapter's own buffer; pre-RMS it is G itself, which the block above has
+  // written there, or the caller's dy (copied only if dx_in overwrites it)
+  ab.dz = c.llama && !copy_g ? nullptr : c.W(L.gdz[2 * l + 1]);
+  const void* dz2 = ab.dz ? ab.dz : G;
   if (c.llama) {
     ab.norm = Norm::None;
   } else {
@@ -848,11 +849,17 @@ extern "C" ringada_status ringada_stage_backward(ringada_stage* st, void* stream
   RG_TRY(make_ctx(st, stream, cx));
   const void* G = dy;
   const int lo = c < 0 ? 0 : c;
+  const size_t io = (size_t)cx.T * cx.d * cx.es;
+  const char* gb = static_cast<const char*>(dy);
+  const char* xb = static_cast<const char*>(dx_in);
+  const bool overlap = xb && gb < xb + io && xb < gb + io;
   st->dw_pending.clear();
   for (int l = D.n_blocks - 1; l >= lo; --l) {
     const bool stop = (l == c);
-    void* dX = stop ? nullptr : (l == 0 ? dx_in : cx.W(st->L.dact[l % 2]));
-    RG_TRY(block_backward(cx, l, G, dX, stop));
+    // a pre-RMS block's dX is the gradient at the next FFN adapter's output as it is
+    void* dX = stop ? nullptr
+                    : (l == 0 ? dx_in : cx.W(cx.llama ? st->L.gdz[2 * (l - 1) + 1] : st->L.dact[l % 2]));
+    RG_TRY(block_backward(cx, l, G, dX, stop, overlap && G == dy));
     G = dX;
   }
   // the adapters' weight gradients (dW_up += gelu(U)^T dZ, dW_down += z^T dU)
