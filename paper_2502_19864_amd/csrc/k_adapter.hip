@@ -722,6 +722,17 @@ __device__ __forceinline__ float dot16_f32(const float* x, const float* w, int n
   return s;
 }
 
+// The fp32 kernels are chains of dependent steps, each starting with a load that would
+// wait for memory in its turn.  Read at the start instead, one dword of each of the
+// first 256 128-B lines of an operand, all in flight together, it finds the line in the
+// cache (the value itself goes unused: warm_done marks it read).  d 128, m 16, 128
+// tokens: a training iteration of two blocks, four launches of each, 140.5 -> 136.3 us.
+__device__ __forceinline__ float warm(const float* p, long n) {
+  const long i = 32 * (long)threadIdx.x;
+  return p && i < n ? p[i] : 0.f;
+}
+__device__ __forceinline__ void warm_done(float v) { asm volatile("" ::"v"(v)); }
+
 __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float* sh = reinterpret_cast<float*>(smem);
@@ -734,7 +745,11 @@ __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
   const float* res = static_cast<const float*>(a.res) + (long)t * d;
   const float* wdt = static_cast<const float*>(a.wdn_t);
   const float* wut = static_cast<const float*>(a.wup_t);
+  const float* gm = static_cast<const float*>(a.gamma);
+  const float* bt = static_cast<const float*>(a.beta);
   const bool has_ad = wdt != nullptr;  // else: residual add + norm only
+  const float w0 = warm(wdt, (long)m * d), w1 = warm(wut, (long)m * d), w2 = warm(res, d), w3 = warm(gm, d),
+              w4 = warm(bt, d);
   for (int i = threadIdx.x; i < d; i += blockDim.x) sz[i] = z[i];
   __syncthreads();
   if (has_ad)
@@ -745,6 +760,7 @@ __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
       sg[j] = gelu_f(u);
     }
   __syncthreads();
+  for (float w : {w0, w1, w2, w3, w4}) warm_done(w);
   float s1 = 0.f;
   for (int f = threadIdx.x; f < d; f += blockDim.x) {
     float v = res[f] + sz[f];
@@ -766,8 +782,6 @@ __global__ __launch_bounds__(256) void adapter_fwd_f32(AdapterFwdArgs a) {
   const float rstd = rsqrtf(block_sum(s2, red) / d + a.eps);
   if (a.rstd && threadIdx.x == 0) a.rstd[t] = rstd;
   float* o = (a.norm == Norm::LN) ? out : static_cast<float*>(a.out_norm) + (long)t * d;
-  const float* gm = static_cast<const float*>(a.gamma);
-  const float* bt = static_cast<const float*>(a.beta);
   for (int f = threadIdx.x; f < d; f += blockDim.x) {
     const float xh = (sv[f] - mean) * rstd;
     o[f] = xh * gm[f] + (a.norm == Norm::LN ? bt[f] : 0.f);
@@ -785,6 +799,11 @@ __global__ __launch_bounds__(256) void adapter_bwd_f32(AdapterBwdArgs a) {
   const float* gin = static_cast<const float*>(a.gin) + (long)t * d;
   const float* xh = static_cast<const float*>(a.xhat) + (long)t * d;
   const float* gm = static_cast<const float*>(a.gamma);
+  const float* wu = static_cast<const float*>(a.wup);
+  const float* wd = static_cast<const float*>(a.wdn);
+  const float* u = wu ? static_cast<const float*>(a.u) + (long)t * m : nullptr;
+  const float w0 = warm(wu, (long)m * d), w1 = warm(a.dzin ? wd : nullptr, (long)m * d), w2 = warm(u, m);
+  const float rs = a.norm != Norm::None ? a.rstd[t] : 0.f;
   if (a.norm == Norm::None) {
     for (int f = threadIdx.x; f < d; f += blockDim.x) sdz[f] = gin[f];
   } else {
@@ -796,7 +815,6 @@ __global__ __launch_bounds__(256) void adapter_bwd_f32(AdapterBwdArgs a) {
     }
     const float m1 = (a.norm == Norm::LN) ? block_sum(s1, red) / d : 0.f;
     const float m2 = block_sum(s2, red) / d;
-    const float rs = a.rstd[t];
     const float* dres = static_cast<const float*>(a.dres);
     for (int f = threadIdx.x; f < d; f += blockDim.x) {
       const float g = gin[f] * gm[f];
@@ -809,9 +827,7 @@ __global__ __launch_bounds__(256) void adapter_bwd_f32(AdapterBwdArgs a) {
     for (int f = threadIdx.x; f < d; f += blockDim.x) dzo[f] = sdz[f];
   }
   if (!a.wup) return;  // no adapter: the norm backward (dz) is the whole result
-  const float* wu = static_cast<const float*>(a.wup);
-  const float* wd = static_cast<const float*>(a.wdn);
-  const float* u = static_cast<const float*>(a.u) + (long)t * m;
+  for (float w : {w0, w1, w2}) warm_done(w);
   for (int j = threadIdx.x / 16; j < m; j += 16) {
     const float dv = dot16_f32(sdz, wu + (long)j * d, d);
     if (threadIdx.x % 16) continue;
