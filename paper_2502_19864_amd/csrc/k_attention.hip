@@ -27,7 +27,7 @@ namespace rg {
 // row-major source into LDS row-major (pitch DH + 8), in two steps so that the
 // caller can issue the global loads of several tiles before the first LDS
 // store: issue() loads this thread's 16-B chunks into registers, store()
-// writes them, rotating pairs (i, i + DH/2) when rot.
+// writes them.
 template <int DH, int NT>
 struct TileLoad {
   static constexpr int HC = DH / 16, PAIRS = KT * HC, IT = PAIRS / NT;
@@ -45,35 +45,17 @@ struct TileLoad {
       raw[it][1] = ld_frag(a0 + DH / 2);
     }
   }
-  __device__ __forceinline__ void store(bf16* dst, bool rot, int S, int r0, const float2* rtab) {
+  __device__ __forceinline__ void store(bf16* dst, int S, int r0) {
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int p = threadIdx.x + it * NT;
       const int r = p / HC, c = p % HC, row = r0 + r;
       if (row >= S) raw[it][0] = raw[it][1] = zero_frag();
-      if (rot && row < S) {
-        float x1[8], x2[8];
-        unpack_frag(raw[it][0], x1);
-        unpack_frag(raw[it][1], x2);
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          float cs, sn;
-          rope_cs(rtab, row, c * 8 + v, DH, &cs, &sn);
-          const float a = x1[v], bb = x2[v];
-          x1[v] = a * cs - bb * sn;
-          x2[v] = bb * cs + a * sn;
-        }
-        raw[it][0] = pack_frag(x1);
-        raw[it][1] = pack_frag(x2);
-      }
       *reinterpret_cast<bf16x8*>(dst + r * (DH + 8) + c * 8) = raw[it][0];
       *reinterpret_cast<bf16x8*>(dst + r * (DH + 8) + c * 8 + DH / 2) = raw[it][1];
     }
   }
 };
-
-// Q and K need the rotation as they are loaded (it is not already in qkv)
-__device__ __forceinline__ bool rot_load(const AttnArgs& a) { return a.rope && !a.rope_in_qkv; }
 
 // Fragments (B operand, k = head dim) of one row held by this lane: dims
 // 16s + 8*(lane/32) + v, zero when !valid (src is a valid row even then: the loads are
@@ -540,7 +522,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
   const bf16* qkv = static_cast<const bf16*>(a.qkv);
   const bf16* dO = static_cast<const bf16*>(a.dout);
 
-  // Q, dO, K, V tiles (rows >= S zero; RoPE on Q and K), this lane's O row
+  // Q, dO, K, V tiles (rows >= S zero), this lane's O row
   // and its LSE, every global load issued before the first LDS store, none
   // conditional on a lane (rows past S read a valid row, masked afterwards).  The
   // prologue is bound by memory bandwidth (all workgroups load at once), so
@@ -560,10 +542,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 6
     for (int s = 0; s < DH / 16; ++s) orw[s] = ld_frag(orow + 16 * s + 8 * half);  // qrow clamped
   }
   const float lse_raw = a.lse[(long)bh * S + (qv ? q : 0)];
-  tq.store(sQ, rot_load(a), S, 0, rtab);
-  tdo.store(sdO, false, S, 0, rtab);
-  tk.store(sK, rot_load(a), S, 0, rtab);
-  tv.store(sV, false, S, 0, rtab);
+  tq.store(sQ, S, 0);
+  tdo.store(sdO, S, 0);
+  tk.store(sK, S, 0);
+  tv.store(sV, S, 0);
   __syncthreads();
   // the O row and the LSE were loaded last; masked only here, at their first use
   const float lse = qv ? lse_raw : 0.f;
@@ -949,7 +931,8 @@ static hipError_t check(int dtype, const AttnArgs& a, bool bwd) {
   if (a.B <= 0 || a.S <= 0 || a.H <= 0 || !a.qkv || !a.o || !a.lse) return hipErrorInvalidValue;
   if (bwd && (!a.dout || !a.dsum || !a.dqkv)) return hipErrorInvalidValue;
   if (a.rope && (!a.rope_tab || a.rope_rows < a.S)) return hipErrorInvalidValue;
-  if (a.rope_in_qkv && (!a.rope || dtype != DT_BF16)) return hipErrorInvalidValue;
+  // bf16: Q and K arrive rotated, or there is no rotation
+  if (a.rope_in_qkv != a.rope || (a.rope && dtype != DT_BF16)) return hipErrorInvalidValue;
   const int d = a.H * a.dh;
   const bool three_block = a.qkv_hs == a.dh && a.qkv_ko == d && a.qkv_vo == 2 * d;
   const bool per_head = a.qkv_hs == 3 * a.dh && a.qkv_ko == a.dh && a.qkv_vo == 2 * a.dh;
