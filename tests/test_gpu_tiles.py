@@ -2,12 +2,11 @@
 and of the loss helpers' remaining instantiations, through the C ABI.
 
 The GEMM launcher picks a tile shape per call from (tokens, N, K) and the
-epilogue (pipelined 128x192, 128x96, 128x128 with two or three stages,
-256x192 and 256x128 with eight waves, and the split of a half-empty last
-round of 256x128 tiles onto 128x128).  The stage workloads of the other
-tests reach about half of the legal (role, epilogue, tile) combinations.
-The one-block stages below reach every other one (each entry lists what it
-adds), at token counts up to 32768.  Outputs of at most 32 MiB are stored
+epilogue.  The stage workloads of the other tests reach about half of the
+legal (role, epilogue, tile) combinations.
+The one-block stages below are at the edges of the larger tiles' ranges (each
+entry lists the shapes it was made for), at token counts up to 32768;
+test_gpu_tile_choice covers the smaller tiles.  Outputs of at most 32 MiB are stored
 with the non-temporal hint, larger ones plainly: the 32768-token d = 1024
 case runs the plain arm of the projection GEMMs, the fused attention and the
 adapter rows.
