@@ -711,12 +711,13 @@ __global__ __launch_bounds__(HEAD_NT) void head_ce_many_k(const T* y, int B, int
   if (first && t == 0 && loss) *loss = lold + lacc;
 }
 
-// dY in the place of y: one workgroup for all features, so that no row is
-// written before its logits are formed.  Samples go in chunks of HEAD_CHUNK: one
-// wave per sample for the logits, the softmax and the loss (into LDS), then one
-// thread per feature (in blocks of HEAD_NT features) for the dY rows and the
-// W_h gradient, thread c for the bias gradient of class c and thread 0 for
-// the loss.  The other workgroups zero rows 1..S-1 of every sequence.
+// dY in the place of y: one workgroup for all features.  Samples go in chunks of
+// HEAD_CHUNK: one wave per sample for the logits, the softmax and the loss (into
+// LDS), then, once the logits of the whole chunk are formed, one thread per
+// feature (in blocks of HEAD_NT features) for the dY rows and the W_h gradient, so
+// that a row is overwritten only after its last use; thread c for the bias
+// gradient of class c and thread 0 for the loss.  The other workgroups zero rows
+// 1..S-1 of every sequence.
 template <typename T, int CN>  // CN: class count bound, compile time (the loops over classes unroll)
 __global__ __launch_bounds__(HEAD_NT) void head_ce_inplace_k(const T* y, int B, int S, int d, const float* wh,
                                                      const float* bh, int C_, const int* labels, T* dy, float* gwh,
@@ -761,60 +762,48 @@ __global__ __launch_bounds__(HEAD_NT) void head_ce_inplace_k(const T* y, int B, 
       }
     }
   };
-  // A batch of at most HEAD_CHUNK samples has its logits formed once; larger
-  // batches re-form each chunk's for every block of HEAD_NT features.
-  const bool one_chunk = B <= HEAD_CHUNK;
   float bacc = 0.f, lacc = 0.f;
-  for (int fb = 0; fb * HEAD_NT < d; ++fb) {
-    const int i = t + fb * HEAD_NT;
-    const bool iv = i < d;
-    float wv[CN], gacc[CN];
+  for (int b0 = 0; b0 < B; b0 += HEAD_CHUNK) {
+    const int nb = min(HEAD_CHUNK, B - b0);
+    if (b0 > 0) __syncthreads();  // every thread is done with the last chunk's sdl / sls
+    logits(b0, nb);
+    __syncthreads();
+    for (int i = t; i < d; i += HEAD_NT) {
+      float wv[CN], gacc[CN];
 #pragma unroll
-    for (int c = 0; c < CN; ++c) {
-      wv[c] = (iv && c < C) ? wh[(long)i * C + c] : 0.f;
-      gacc[c] = 0.f;
-    }
-    for (int b0 = 0; b0 < B; b0 += HEAD_CHUNK) {
-      const int nb = min(HEAD_CHUNK, B - b0);
-      if (fb == 0 || !one_chunk) {  // the same for every thread
-        logits(b0, nb);
-        __syncthreads();
+      for (int c = 0; c < CN; ++c) {
+        wv[c] = c < C ? wh[(long)i * C + c] : 0.f;
+        gacc[c] = 0.f;
       }
       // dY row and the W_h gradient of feature i (thread = feature), the samples in
       // order; UNR samples' loads in flight at once (clamped, masked after)
       constexpr int UNR = CN <= 4 ? 8 : 4;
-      if (iv)
-        for (int sm0 = 0; sm0 < nb; sm0 += UNR) {
-          float yv[UNR];
+      for (int sm0 = 0; sm0 < nb; sm0 += UNR) {
+        float yv[UNR];
 #pragma unroll
-          for (int u = 0; u < UNR; ++u) yv[u] = St<T>::ld(y, (long)(b0 + min(sm0 + u, nb - 1)) * S * d + i);
+        for (int u = 0; u < UNR; ++u) yv[u] = St<T>::ld(y, (long)(b0 + min(sm0 + u, nb - 1)) * S * d + i);
 #pragma unroll
-          for (int u = 0; u < UNR; ++u) {
-            const int sm = sm0 + u;
-            if (sm >= nb) break;
-            float g = 0.f;
+        for (int u = 0; u < UNR; ++u) {
+          const int sm = sm0 + u;
+          if (sm >= nb) break;
+          float g = 0.f;
 #pragma unroll
-            for (int c = 0; c < CN; ++c)
-              if (c < C) {
-                gacc[c] += yv[u] * sdl[sm][c];
-                g += sdl[sm][c] * wv[c];
-              }
-            St<T>::st_nt(dy, (long)(b0 + sm) * S * d + i, g);
-          }
+          for (int c = 0; c < CN; ++c)
+            if (c < C) {
+              gacc[c] += yv[u] * sdl[sm][c];
+              g += sdl[sm][c] * wv[c];
+            }
+          St<T>::st_nt(dy, (long)(b0 + sm) * S * d + i, g);
         }
-      if (fb == 0) {  // the bias gradient and the loss, once
-        if (t < C)
-          for (int sm = 0; sm < nb; ++sm) bacc += sdl[sm][t];
-        if (t == 0)
-          for (int sm = 0; sm < nb; ++sm) lacc += sls[sm];
       }
-      if (!one_chunk) __syncthreads();  // the next chunk overwrites sdl / sls
-    }
-    if (iv) {
 #pragma unroll
       for (int c = 0; c < CN; ++c)
-        if (c < C) gwh[(long)i * C + c] += gacc[c];
+        if (c < C) gwh[(long)i * C + c] += gacc[c];  // chunk by chunk, by this thread alone
     }
+    if (t < C)
+      for (int sm = 0; sm < nb; ++sm) bacc += sdl[sm][t];
+    if (t == 0)
+      for (int sm = 0; sm < nb; ++sm) lacc += sls[sm];
   }
   if (t < C) gbh[t] += bacc;
   if (t == 0 && loss) *loss += lacc;

@@ -1,7 +1,8 @@
 """ringada_head_ce over many workgroups: widths at the edges of the 64-feature
 blocks, batches at the edges of the 16 waves and of two samples per wave,
 sequences of one position (no rows to zero), and dY in the place of y (the one
-workgroup for all features).  Bounds as in test_gpu_tiles: fp32 sums of exact
+workgroup for all features), there also with several chunks of 256 samples and
+several blocks of 1024 features.  Bounds as in test_gpu_tiles: fp32 sums of exact
 inputs 1e-4, the bf16 dY two units in the last place."""
 import numpy as np
 import pytest
@@ -16,7 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n_classes,batch,seq,d,inplace", [
     (2, 1, 1, 8, False), (2, 16, 3, 64, False), (2, 17, 2, 72, False), (2, 33, 1, 776, False), (3, 15, 2, 56, False),
-    (16, 18, 2, 136, False), (1, 5, 2, 128, False), (2, 33, 3, 776, True), (5, 20, 2, 1032, True)])
+    (16, 18, 2, 136, False), (1, 5, 2, 128, False), (2, 33, 3, 776, True), (5, 20, 2, 1032, True),
+    (2, 257, 1, 1024, True), (2, 300, 2, 2048, True), (5, 300, 1, 1032, True), (16, 513, 2, 2056, True)])
 def test_head_blocks(dtype, n_classes, batch, seq, d, inplace):
     import torch
     if not torch.cuda.is_available():
