@@ -257,7 +257,11 @@ ringada_status ringada_adapter_step(ringada_stage* st, void* stream,
  * updates the head; these produce the dy that enters the backward. */
 
 /* Mean squared error over n elements: dy = 2 (y - target) / n, *loss = mean.
- * y, target, dy in `dtype`; loss is one device float (may be NULL). */
+ * y, target, dy in `dtype`; loss is one device float (may be NULL).  dy may be
+ * y or target itself; any other overlap with them returns RINGADA_E_INVALID.
+ * In place the call runs on one compute unit: far slower for large tensors (3.1 M
+ * bf16 elements: 200 us against 6).  While a call with a loss runs, the first 4 KB
+ * of dy may hold partial sums. */
 ringada_status ringada_loss_mse(void* stream, int32_t dtype, const void* y,
                                 const void* target, int64_t n, void* dy,
                                 float* loss);
@@ -268,7 +272,11 @@ ringada_status ringada_loss_mse(void* stream, int32_t dtype, const void* y,
  * labels [batch] int32 in [0, n_classes); the fp32 gradients g_wh, g_bh and
  * the mean loss (one device float, may be NULL) are ADDED into: zero them
  * before the first call of an accumulation.  n_classes <= 16; d a multiple of
- * 8; y, dy and w_h 16-B aligned.  Every sum runs over the samples in a fixed
+ * 8; y, dy and w_h 16-B aligned.  dy may be y itself; any other overlap with
+ * position 0 of a sequence of y returns RINGADA_E_INVALID.  In place one compute
+ * unit forms all rows of position 0: slower (32 samples, d 768, two classes: 9 us
+ * against 6; 128 samples, d 4096: 101 against 40, with 16 classes 3.9 ms against
+ * 0.1).  Every sum runs over the samples in a fixed
  * order: the same inputs give the same bits. */
 ringada_status ringada_head_ce(void* stream, int32_t dtype, const void* y,
                                int32_t batch, int32_t seq, int32_t d,

@@ -412,16 +412,26 @@ __global__ __launch_bounds__(MSE_MAX_WG) void mse_finish_k(const T* y, const T* 
   for (long i = threadIdx.x; i < skip; i += MSE_MAX_WG) St<T>::st(dy, i, sc * (St<T>::ld(y, i) - St<T>::ld(t, i)));
 }
 
+// dY may be clear of an input or in its place, element on element; shifted over it,
+// threads would overwrite elements that others have yet to read
+bool mse_dy_ok(const void* y, const void* t, const void* dy, size_t bytes) {
+  const uintptr_t pd = reinterpret_cast<uintptr_t>(dy);
+  for (const void* in : {y, t}) {
+    const uintptr_t p = reinterpret_cast<uintptr_t>(in);
+    if (p != pd && p < pd + bytes && pd < p + bytes) return false;
+  }
+  return true;
+}
+
 template <typename T>
 static hipError_t mse(const T* y, const T* t, long n, T* dy, float* loss, hipStream_t s) {
   const uintptr_t py = reinterpret_cast<uintptr_t>(y), pt = reinterpret_cast<uintptr_t>(t),
                   pd = reinterpret_cast<uintptr_t>(dy), bytes = (uintptr_t)n * sizeof(T);
   const bool vec = ((py | pt | pd) & 15u) == 0;
-  // in place (dY on y or the target): the partial sums would overwrite inputs
-  const bool overlap = (pd < py + bytes && py < pd + bytes) || (pd < pt + bytes && pt < pd + bytes);
+  const bool inplace = pd == py || pd == pt;  // the partial sums would overwrite inputs
   constexpr int NT = 256, U = 2;
   constexpr long VE = 16 / sizeof(T);
-  if ((long)bytes <= MSE_ONE_BYTES || overlap) {
+  if ((long)bytes <= MSE_ONE_BYTES || inplace) {
     RG_LAUNCH((mse_k<T, 1024, 4>), dim3(1), dim3(1024), 0, s, y, t, n, dy, loss, 0L, vec);
     return hipGetLastError();
   }
@@ -436,7 +446,7 @@ static hipError_t mse(const T* y, const T* t, long n, T* dy, float* loss, hipStr
 }
 
 hipError_t launch_mse(int dtype, const void* y, const void* t, long n, void* dy, float* loss, hipStream_t s) {
-  if (!y || !t || !dy || n <= 0) return hipErrorInvalidValue;
+  if (!y || !t || !dy || n <= 0 || !mse_dy_ok(y, t, dy, n * (dtype == DT_BF16 ? 2 : 4))) return hipErrorInvalidValue;
   if (dtype == DT_BF16) return mse(static_cast<const bf16*>(y), static_cast<const bf16*>(t), n, static_cast<bf16*>(dy), loss, s);
   return mse(static_cast<const float*>(y), static_cast<const float*>(t), n, static_cast<float*>(dy), loss, s);
 }
@@ -809,6 +819,17 @@ __global__ __launch_bounds__(HEAD_NT) void head_ce_inplace_k(const T* y, int B, 
   if (t == 0 && loss) *loss += lacc;
 }
 
+// dY may be in the place of y, or clear of the rows of y that are read (position 0 of
+// each sequence); otherwise some would be overwritten before their logits are formed
+bool head_dy_ok(const void* y, const void* dy, int B, int S, size_t row) {
+  if (y == dy) return true;
+  const uintptr_t py = reinterpret_cast<uintptr_t>(y), pd = reinterpret_cast<uintptr_t>(dy);
+  const uintptr_t step = (uintptr_t)S * row, end = pd + (uintptr_t)B * step;
+  // the first of those rows that ends past dY's start
+  const uintptr_t b = pd < py + row ? 0 : (pd - py - row) / step + 1;
+  return b >= (uintptr_t)B || py + b * step >= end;
+}
+
 hipError_t launch_head_ce(int dtype, const void* y, int B, int S, int d, const float* wh, const float* bh,
                           int C, const int* labels, void* dy, float* gwh, float* gbh, float* loss,
                           hipStream_t s) {
@@ -821,19 +842,17 @@ hipError_t launch_head_ce(int dtype, const void* y, int B, int S, int d, const f
     return hipErrorInvalidValue;
   const long nvec = (long)B * (S - 1) * (long)(d * es / 16);
   const int nz = (int)std::min<long>(255, (nvec + HEAD_NT - 1) / HEAD_NT);
-  const char* yb = static_cast<const char*>(y);
-  const char* db = static_cast<const char*>(dy);
-  const size_t bytes = (size_t)B * S * d * es;
-  const bool overlap = yb < db + bytes && db < yb + bytes;
-  const int nf = overlap ? 1 : (d + HEAD_F - 1) / HEAD_F;
+  if (!head_dy_ok(y, dy, B, S, d * es)) return hipErrorInvalidValue;
+  const bool inplace = y == dy;
+  const int nf = inplace ? 1 : (d + HEAD_F - 1) / HEAD_F;
   const dim3 grid(nf + nz), block(HEAD_NT);
   auto go = [&](auto T0) {
     using T = decltype(T0);
     const T* yt = static_cast<const T*>(y);
     T* dt = static_cast<T*>(dy);
-    if (overlap && C == 2)
+    if (inplace && C == 2)
       RG_LAUNCH((head_ce_inplace_k<T, 2>), grid, block, 0, s, yt, B, S, d, wh, bh, C, labels, dt, gwh, gbh, loss);
-    else if (overlap)
+    else if (inplace)
       RG_LAUNCH((head_ce_inplace_k<T, HEAD_C>), grid, block, 0, s, yt, B, S, d, wh, bh, C, labels, dt, gwh, gbh,
                 loss);
     else if (C == 2)

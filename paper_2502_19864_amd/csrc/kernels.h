@@ -224,6 +224,9 @@ hipError_t launch_adapter_sync(int dtype, const AdapterSlot* slots, int n_slots,
                                hipStream_t s);
 
 // ---------------------------------------------------------------- losses
+// whether dY overlaps the inputs in no other way than the losses can take
+bool mse_dy_ok(const void* y, const void* t, const void* dy, size_t bytes);
+bool head_dy_ok(const void* y, const void* dy, int B, int S, size_t row_bytes);
 hipError_t launch_mse(int dtype, const void* y, const void* t, long n, void* dy, float* loss,
                       hipStream_t s);
 hipError_t launch_head_ce(int dtype, const void* y, int B, int S, int d, const float* wh,

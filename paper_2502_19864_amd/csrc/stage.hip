@@ -900,6 +900,8 @@ extern "C" ringada_status ringada_loss_mse(void* stream, int32_t dtype, const vo
                                            void* dy, float* loss) {
   if (dtype != RINGADA_F32 && dtype != RINGADA_BF16) return fail(RINGADA_E_INVALID, "unknown dtype");
   if (!y || !target || !dy || n <= 0) return fail(RINGADA_E_INVALID, "bad argument");
+  if (!mse_dy_ok(y, target, dy, (size_t)n * (dtype == RINGADA_BF16 ? 2 : 4)))
+    return fail(RINGADA_E_INVALID, "dy overlaps y or target without being the same tensor");
   RG_HIP(launch_mse(dtype, y, target, n, dy, loss, static_cast<hipStream_t>(stream)));
   return RINGADA_OK;
 }
@@ -910,6 +912,8 @@ extern "C" ringada_status ringada_head_ce(void* stream, int32_t dtype, const voi
   if (dtype != RINGADA_F32 && dtype != RINGADA_BF16) return fail(RINGADA_E_INVALID, "unknown dtype");
   if (!y || !w_h || !b_h || !labels || !dy || !g_wh || !g_bh) return fail(RINGADA_E_INVALID, "NULL argument");
   if (batch < 1 || seq < 1 || d < 1 || n_classes < 1 || n_classes > 16) return fail(RINGADA_E_INVALID, "bad size");
+  if (!head_dy_ok(y, dy, batch, seq, (size_t)d * (dtype == RINGADA_BF16 ? 2 : 4)))
+    return fail(RINGADA_E_INVALID, "dy overlaps rows of y that the loss reads without being y");
   RG_HIP(launch_head_ce(dtype, y, batch, seq, d, w_h, b_h, n_classes, labels, dy, g_wh, g_bh, loss,
                         static_cast<hipStream_t>(stream)));
   return RINGADA_OK;

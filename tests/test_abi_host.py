@@ -191,3 +191,24 @@ def test_state_machine_on_an_unbound_stage():
         assert "SGD" in B.ringada_last_error()
     finally:
         B.ringada_stage_destroy(h)
+
+
+@pytest.mark.parametrize("dtype,es", [(B.BF16, 2), (B.F32, 4)])
+def test_losses_refuse_a_shifted_dy(dtype, es):
+    """A dY that lies over an input without being it would overwrite elements
+    before they are read: refused on the host, before the device is touched."""
+    base, n = 1 << 30, 1000
+    nb = n * es
+    for y, t, dy in ((base, base + (1 << 20), base + 16), (base + 16, base + (1 << 20), base),
+                     (base + (1 << 20), base, base + nb - es), (base + nb - es, base + (1 << 20), base),
+                     (base, base + es, base)):
+        with pytest.raises(B.RingadaError) as e:
+            B.ringada_loss_mse(None, dtype, y, t, n, dy, None)
+        assert e.value.status == B.RINGADA_E_INVALID and "overlaps" in B.ringada_last_error()
+    batch, seq, d = 3, 4, 64
+    row = d * es
+    far = base + (1 << 20)
+    for shift in (16, row, -16, -row, 4 * row, 8 * row, 8 * row + row - 16, -(11 * row), -(12 * row) + 16):
+        with pytest.raises(B.RingadaError) as e:
+            B.ringada_head_ce(None, dtype, base, batch, seq, d, far, far, 2, far, base + shift, far, far, None)
+        assert e.value.status == B.RINGADA_E_INVALID and "overlaps" in B.ringada_last_error(), shift

@@ -2,7 +2,8 @@
 blocks, batches at the edges of the 16 waves and of two samples per wave,
 sequences of one position (no rows to zero), and dY in the place of y (the one
 workgroup for all features), there also with several chunks of 256 samples and
-several blocks of 1024 features.  Bounds as in test_gpu_tiles: fp32 sums of exact
+several blocks of 1024 features.  dY over rows of y that are not read is a call like
+any other.  Bounds as in test_gpu_tiles: fp32 sums of exact
 inputs 1e-4, the bf16 dY two units in the last place."""
 import numpy as np
 import pytest
@@ -18,7 +19,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n_classes,batch,seq,d,inplace", [
     (2, 1, 1, 8, False), (2, 16, 3, 64, False), (2, 17, 2, 72, False), (2, 33, 1, 776, False), (3, 15, 2, 56, False),
     (16, 18, 2, 136, False), (1, 5, 2, 128, False), (2, 33, 3, 776, True), (5, 20, 2, 1032, True),
-    (2, 257, 1, 1024, True), (2, 300, 2, 2048, True), (5, 300, 1, 1032, True), (16, 513, 2, 2056, True)])
+    (2, 257, 1, 1024, True), (2, 300, 2, 2048, True), (5, 300, 1, 1032, True), (16, 513, 2, 2056, True),
+    (2, 17, 3, 72, "past"), (5, 3, 2, 136, "past")])
 def test_head_blocks(dtype, n_classes, batch, seq, d, inplace):
     import torch
     if not torch.cuda.is_available():
@@ -35,7 +37,11 @@ def test_head_blocks(dtype, n_classes, batch, seq, d, inplace):
     runs = []
     for _ in range(2):
         src = yt.clone()
-        dyt = src if inplace else torch.full_like(yt, float("nan"))
+        dyt = src if inplace is True else torch.full_like(yt, float("nan"))
+        if inplace == "past":  # over the rows of y past its last position 0, which nobody reads
+            buf = torch.full((2 * yt.numel(),), float("nan"), dtype=tdt, device="cuda")
+            src, dyt = buf[:yt.numel()].view_as(yt), buf[yt.numel() - (seq - 1) * d:][:yt.numel()].view_as(yt)
+            src.copy_(yt)
         gwh, gbh, loss = dev(gwh0), dev(gbh0), torch.full((1,), 2.0, device="cuda")
         B.ringada_head_ce(s, B.BF16 if dtype == "bf16" else B.F32, src, batch, seq, d, wht, bht, n_classes, labt, dyt,
                           gwh, gbh, loss)
