@@ -117,7 +117,10 @@ typedef struct {
  * The backward ADDS into g_down/g_up; ringada_adapter_step consumes and zeroes
  * them.  g_down and g_up must be 16-byte aligned (ringada_stage_bind_block
  * returns RINGADA_E_INVALID otherwise); the bf16 backward sums each gradient
- * element in a fixed order, so equal inputs give bitwise equal gradients. */
+ * element in a fixed order, so equal inputs give bitwise equal gradients.
+ * Adapters of one stage may share g_down and g_up (the backward then adds every
+ * one's gradient); ringada_adapter_step takes all four tensors of each adapter
+ * as its own, so a stage that shares any updates them some other way. */
 typedef struct {
   float* w_down; /* [d, m] */
   float* w_up;   /* [m, d] */

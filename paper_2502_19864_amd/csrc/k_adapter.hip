@@ -1059,6 +1059,24 @@ long adapter_dw_part_bytes(int dtype, int T, int d, int m, int n_adapters) {
   return nb * 2 * ((T + DW_TC - 1) / DW_TC) * (long)d * m * 4;
 }
 
+// How many of a[0 .. n-1] go into one launch: up to DW_BATCH, and none that adds into
+// memory another of them adds into (stage adapters may share gradients; within a
+// launch one of two additions to an element could be lost).
+static int dw_launch_len(const AdapterDwArgs* a, int n) {
+  const size_t bytes = (size_t)a[0].m * a[0].d * sizeof(float);
+  auto meet = [&](const float* p, const float* q) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(p), y = reinterpret_cast<uintptr_t>(q);
+    return x < y + bytes && y < x + bytes;
+  };
+  const int most = n < DW_BATCH ? n : DW_BATCH;
+  for (int k = 1; k < most; ++k)
+    for (int j = 0; j < k; ++j)
+      if (meet(a[k].g_up, a[j].g_up) || meet(a[k].g_down, a[j].g_down) || meet(a[k].g_up, a[j].g_down) ||
+          meet(a[k].g_down, a[j].g_up))
+        return k;
+  return most;
+}
+
 hipError_t launch_adapter_dw_batch(int dtype, const AdapterDwArgs* a, int n, float* part, long part_bytes,
                                    hipStream_t s) {
   if (n < 0 || (n > 0 && !a)) return hipErrorInvalidValue;
@@ -1071,8 +1089,8 @@ hipError_t launch_adapter_dw_batch(int dtype, const AdapterDwArgs* a, int n, flo
   if (dtype != DT_BF16) {
     for (int k = 1; k < n; ++k)
       if (a[k].T != a[0].T || a[k].d != a[0].d || a[k].m != a[0].m) return hipErrorInvalidValue;
-    for (int k0 = 0; k0 < n; k0 += DW_BATCH) {
-      const int nb = n - k0 < DW_BATCH ? n - k0 : DW_BATCH;
+    for (int k0 = 0, nb; k0 < n; k0 += nb) {
+      nb = dw_launch_len(a + k0, n - k0);
       AdapterDwBatch b{};
       for (int k = 0; k < nb; ++k) b.a[k] = a[k0 + k];
       RG_LAUNCH(adapter_dw_f32, dim3((unsigned)((a[0].m + 15) / 16 * ((a[0].d + 15) / 16)), 2 * nb),
@@ -1089,8 +1107,8 @@ hipError_t launch_adapter_dw_batch(int dtype, const AdapterDwArgs* a, int n, flo
   }
   if (!part || !al16(part) || part_bytes < adapter_dw_part_bytes(dtype, a[0].T, a[0].d, a[0].m, n))
     return hipErrorInvalidValue;
-  for (int k0 = 0; k0 < n; k0 += DW_BATCH) {
-    const int nb = n - k0 < DW_BATCH ? n - k0 : DW_BATCH;
+  for (int k0 = 0, nb; k0 < n; k0 += nb) {
+    nb = dw_launch_len(a + k0, n - k0);
     AdapterDwBatch b{};
     for (int k = 0; k < nb; ++k) b.a[k] = a[k0 + k];
     b.gx = a[0].d / 64;

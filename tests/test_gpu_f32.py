@@ -7,6 +7,7 @@ import pytest
 
 from gpu_run import run_gpu
 from helpers import TOL, Checker, oracle_run
+from paper_2502_19864_amd import binding as B
 from paper_2502_19864_amd.stage import Stage
 from paper_2502_19864_amd.workloads import Workload, make_inputs
 
@@ -58,3 +59,44 @@ def test_f32_stage_edges(w, cls):
     chk("dx", gpu["dx"], ref["dx"])
     chk.grads(gpu["grads"], ref["grads"], 0, w.n_blocks)
     chk.done()
+
+
+class SharedGrads(Stage):
+    """Every adapter of the stage adds into the first one's gradients."""
+
+    def __init__(self, w, inp):
+        super().__init__(w, inp)
+        first = self.adapters[0][1]
+        for l, pair in enumerate(self.adapters):
+            for t in pair:
+                t.update(g_down=first["g_down"], g_up=first["g_up"])
+            ca = [B.Adapter(**{k: v.data_ptr() for k, v in t.items()}) for t in pair]
+            bw = B.BlockWeights(**{k: v.data_ptr() for k, v in self.frozen[l].items()})
+            B.ringada_stage_bind_block(self.handle, l, bw, None if w.placement == "ffn" else ca[0], ca[1],
+                                       self.block_mem[l], self.block_bytes, self.sptr)
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("dtype,d,f,m,placement", [("f32", 128, 256, 16, "houlsby"), ("f32", 60, 68, 8, "ffn"),
+                                                   ("bf16", 256, 192, 64, "houlsby")])
+def test_shared_gradients_add_up(dtype, d, f, m, placement):
+    """Adapters bound to the same gradient buffers: the backward adds every one's
+    gradient, as one adapter after the other.  The sum of up to six fp32 values
+    of either run differs by their rounding (2^-20 of the largest)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    w = Workload("shared", "bert", dtype, 3, d, 2, f, m, 20, 3, 0, "dy", 2507, placement=placement)
+    inp = make_inputs(w)
+    res = []
+    for cls in (Stage, SharedGrads):
+        print(f"[shared gradients] {dtype} {placement} {cls.__name__}", flush=True)
+        st = cls(w, inp)
+        try:
+            res.append(run_gpu(torch, st, w, inp, -1, want_dx=True)["grads"])
+        finally:
+            st.close()
+    apart, shared = res
+    for k in ("w_down", "w_up"):
+        want = sum(pair[a][k].astype("float64") for pair in apart for a in range(2))
+        assert abs(shared[0][1][k] - want).max() <= 2.0 ** -20 * abs(want).max(), k
