@@ -355,9 +355,12 @@ hipError_t launch_adapter_sync(int dtype, const AdapterSlot* slots, int n_slots,
 // and writes the elements they stood in.  Eight (four) elements per 16-B access
 // when the pointers allow it, U accesses in flight.
 // 3.1 M bf16 elements (32 x 128 x 768): 1007 -> 5.7 us (18.9 MB, 3.3 TB/s).  One
-// workgroup against many: 3.9 and 4.7 us at 64 KB per tensor, 5.4 and 4.6 at
-// 128 KB; the line lies between.
-constexpr long MSE_ONE_BYTES = 96 << 10;
+// workgroup against many, per call, at 64, 128 and 224 KB per tensor: replayed from
+// a graph 4.3 and 4.9, 5.9 and 4.9, 8.7 and 4.9 us; waited for 17.9 and 19.5, 19.6
+// and 19.5, 22.3 and 19.5; in a loop that the host holds up, where the second
+// launch counts, 6.4 and 10.3, 6.4 and 10.4, 8.4 and 10.5.  The line lies where a
+// call that is waited for takes the same.
+constexpr long MSE_ONE_BYTES = 128 << 10;
 constexpr int MSE_MAX_WG = 1024;  // partial sums: one per thread of mse_finish_k
 template <typename T, int NT, int U>
 __global__ __launch_bounds__(NT) void mse_k(const T* y, const T* t, long n, T* dy, float* out, long skip, bool vec) {

@@ -10,7 +10,7 @@ from paper_2502_19864_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
-ONE = 96 << 10  # bytes per tensor up to which one workgroup does it
+ONE = 128 << 10  # bytes per tensor up to which one workgroup does it
 
 
 @pytest.mark.parametrize("dtype,n,offset,inplace,loss", [
