@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_tiles.h"
+
 namespace rg {
 
 // Optional timing of the next launches: when set (by the stage's profiling
@@ -31,25 +33,8 @@ enum { DT_F32 = 0, DT_BF16 = 1 };
 
 // ---------------------------------------------------------------- GEMM
 // C[M, N] = A[M, K] * B[N, K]^T followed by an epilogue.  Both operands are
-// K-contiguous (row strides lda, ldb in elements).
-enum class Epi {
-  Store,    // out = acc (+ bias[n])
-  Gelu,     // pre = acc (+ bias[n]); out2 = pre (if non-null); out = gelu(pre)
-  Resid,    // out = acc + aux[m, n]
-  DGelu,    // out = acc * gelu'(aux[m, n])
-  SwiGlu,   // B rows packed [gate 32 | up 32] per 64; out[m, f] = silu(gate) * up,
-            // out2[m, f] = gate, out2[m, half + f] = up (if non-null)
-  DSwiGlu,  // acc = d(act)[m, f]; aux = [gate | up]; out[m, f] = d gate,
-            // out[m, half + f] = d up
-  Rope,     // bf16 QKV projection, no bias: out = acc with the rotary embedding
-            // applied to columns < rope_cols (Q and K, heads of rope_dh
-            // columns; row m is position m % rope_S)
-  Attn,     // bf16 QKV projection with B rows in per-head order [Q_h K_h V_h]
-            // (d_head 64) and M = sequences of 128 tokens: pre = acc + bias;
-            // out = pre (if non-null); out2[:, 64h..64h+63] = softmax(Q_h K_h^T / 8) V_h
-            // per sequence; lse[(seq * H + h) * 128 + query] (base 2, scaled scores)
-};
-
+// K-contiguous (row strides lda, ldb in elements).  The epilogues, the call sites'
+// names (Role) and the choice of a tile: gemm_tiles.h.
 struct GemmArgs {
   const void* A; int lda;
   const void* B; int ldb;
@@ -66,11 +51,6 @@ struct GemmArgs {
   int nt;  // set by launch_gemm: outputs stored with the non-temporal hint
 };
 
-// Names of the GEMM call sites (each gets its own kernel symbol).
-enum Role {
-  R_QKV_FWD, R_O_FWD, R_FFN_IN_FWD, R_FFN_OUT_FWD,
-  R_QKV_DX, R_O_DX, R_FFN_IN_DX, R_FFN_OUT_DX, N_ROLES
-};
 const char* role_name(Role r);
 
 // Returns hipErrorInvalidValue if the shapes or alignments do not fit the
