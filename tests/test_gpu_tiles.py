@@ -1,15 +1,13 @@
-"""Parity of every tile configuration the bf16 projection GEMMs can select,
-and of the loss helpers' remaining instantiations, through the C ABI.
+"""Parity of the larger tiles that the bf16 projection GEMMs take, and of the
+loss helpers' remaining instantiations, through the C ABI.
 
 The GEMM launcher picks a tile shape per call from (tokens, N, K) and the
-epilogue.  The stage workloads of the other tests reach about half of the
-legal (role, epilogue, tile) combinations.
-The one-block stages below are at the edges of the larger tiles' ranges (each
-entry lists the shapes it was made for), at token counts up to 32768;
-test_gpu_tile_choice covers the smaller tiles.  Outputs of at most 32 MiB are stored
-with the non-temporal hint, larger ones plainly: the 32768-token d = 1024
-case runs the plain arm of the projection GEMMs, the fused attention and the
-adapter rows.
+epilogue.  The one-block stages below take the larger tiles, at token counts up to
+32768 (TILES_TAKE: which, at which call site); test_gpu_tile_choice has the others,
+and test_tile_choice checks both lists against the launcher's own choice.  Outputs of
+at most 32 MiB are stored with the non-temporal hint, larger ones plainly: the
+32768-token d = 1024 case runs the plain arm of the projection GEMMs, the fused
+attention and the adapter rows.
 
 Every op of a block is per sequence, so each case runs the whole batch on
 the GPU and compares three sequences with the oracle: the first, the middle
@@ -46,34 +44,38 @@ def _w(name, arch, d, h, f, seq, batch, seed):
     return Workload(name, arch, "bf16", 1, d, h, f, 64, seq, batch, 0, "dy", seed)
 
 
-# (role, epilogue, tile) combinations each case adds to the rest of the suite
 TILES = {
-    # 128x128 two-stage (>= 512 tiles): SwiGLU, dSwiGLU, FFN-in-dx, FFN-out, O
-    # and O-dx; 128x192 for the rotary QKV's neighbours
     "tiles_llama_d256_t32k": _w("tiles_llama_d256_t32k", "llama", 256, 4, 192, 128, 256, 2101),
-    # 256x192: FFN-out, O, O-dx, QKV-dx (residual), QKV (store); 256x128
-    # FFN-in (GELU) / FFN-out-dx (GELU'); the non-causal two-pass attention at
-    # head dim 128 over two 128-key tiles
+    # also the non-causal two-pass attention at head dim 128 over two 128-row workgroups
     "tiles_bert_d3072_s256": _w("tiles_bert_d3072_s256", "bert", 3072, 24, 192, 256, 16, 2102),
-    # 128x192 O / O-dx / FFN-out / FFN-in-dx (store) and 128x96 QKV-dx /
-    # FFN-in-dx (store) of the pre-RMS block
     "tiles_llama_d768_b64": _w("tiles_llama_d768_b64", "llama", 768, 12, 64, 128, 64, 2103),
-    # 256x192 FFN-in (GELU) / FFN-out-dx (GELU'); 256x128 FFN-in-dx and
-    # QKV-dx (residual)
     "tiles_bert_d2048_f2048": _w("tiles_bert_d2048_f2048", "bert", 2048, 32, 2048, 128, 32, 2104),
-    # 256x192 FFN-in-dx (residual), the rest of the d = 3072 post-LN shapes
     "tiles_bert_d3072_f3072": _w("tiles_bert_d3072_f3072", "bert", 3072, 48, 3072, 128, 32, 2105),
-    # 128x128 two-stage of the post-LN block, QKV-dx included (32768 tokens)
     "tiles_bert_d256_t32k": _w("tiles_bert_d256_t32k", "bert", 256, 4, 64, 128, 256, 2106),
-    # 256x192 of the pre-RMS block's dX GEMMs (store epilogues)
     "tiles_llama_d3072_f576": _w("tiles_llama_d3072_f576", "llama", 3072, 48, 576, 128, 32, 2107),
-    # 128x96 / 128x128 three-stage of the pre-RMS block at 1024 tokens
     "tiles_llama_d768_b8": _w("tiles_llama_d768_b8", "llama", 768, 12, 64, 128, 8, 2108),
-    # 256x128 QKV (store) of the post-LN block: 256x192 would leave CUs idle
     "tiles_bert_d3072_b4": _w("tiles_bert_d3072_b4", "bert", 3072, 48, 64, 256, 4, 2109),
     # outputs past the 32 MiB streaming bound (plain stores): the adapter and norm rows
     # (64 MiB), the QKV projection with the fused attention (192 MiB) and its O rows
     "tiles_bert_d1024_t32k": _w("tiles_bert_d1024_t32k", "bert", 1024, 16, 64, 128, 256, 2110),
+}
+# (call site, tile) pairs each case is there for ("/2": two workgroups to a CU, "/k64":
+# 64-wide k-tiles); the QKV projections at 128 tokens and head width 64 are the fused
+# attention's, on its own tile
+TILES_TAKE = {
+    "tiles_llama_d256_t32k": "qkv_fwd 256x128, o_fwd 256x128, ffn_in_fwd 256x128, ffn_out_fwd 256x128, qkv_dx 256x128, "
+                             "o_dx 256x128, ffn_in_dx 256x128, ffn_out_dx 128x192/2",
+    "tiles_bert_d3072_s256": "qkv_fwd 256x192, o_fwd 256x192, ffn_in_fwd 64x64, ffn_out_fwd 128x192/2, qkv_dx 256x192, "
+                             "o_dx 256x192, ffn_in_dx 128x192/2, ffn_out_dx 64x64",
+    "tiles_llama_d768_b64": "o_fwd 128x192, ffn_in_fwd 64x128, qkv_dx 128x192, o_dx 128x192, ffn_out_dx 32x64",
+    "tiles_bert_d2048_f2048": "ffn_in_fwd 256x128, ffn_out_fwd 256x128, qkv_dx 256x128, ffn_in_dx 256x128, ffn_out_dx 256x128",
+    "tiles_bert_d3072_f3072": "ffn_in_fwd 256x192, ffn_out_fwd 256x192, ffn_in_dx 256x192, ffn_out_dx 256x192",
+    "tiles_bert_d256_t32k": "ffn_in_fwd 128x128, ffn_out_dx 128x128",
+    "tiles_llama_d3072_f576": "o_fwd 256x192, qkv_dx 256x192, o_dx 256x192, ffn_in_dx 128x192/2, ffn_out_dx 128x96",
+    "tiles_llama_d768_b8": "qkv_fwd 128x128, o_fwd 64x64, qkv_dx 64x64, ffn_in_dx 64x128, ffn_out_dx 32x32/2",
+    "tiles_bert_d3072_b4": "o_fwd 128x96, ffn_in_fwd 32x32/2, ffn_out_fwd 128x128/2, qkv_dx 128x96, o_dx 128x96, "
+                           "ffn_in_dx 128x128/2",
+    "tiles_bert_d1024_t32k": "o_fwd 256x256, ffn_in_fwd 128x96, qkv_dx 256x256, o_dx 256x256, ffn_out_dx 128x96",
 }
 
 
@@ -147,9 +149,8 @@ def _head_case(torch, dtype, n_classes, batch=6, seq=5, d=256, seed=2201, repeat
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n_classes,batch,d", [(2, 6, 256), (5, 6, 256), (16, 6, 256), (5, 300, 2048)])
 def test_head_ce_classes(torch, dtype, n_classes, batch, d):
-    """Both instantiations of the head kernel (two classes, and up to 16) in
-    both storage types, and a batch of more than one 256-sample chunk with
-    more than one 1024-feature block.  The loss and the head gradients are
+    """Both head kernels (two classes, and up to 16) in both storage types, and
+    a batch of many 16-sample passes on 32 feature workgroups.  The loss and the head gradients are
     fp32 sums of exact inputs (bound 1e-4); the bf16 dY is one rounding of an
     fp32 dot product (bound: two bf16 units in the last place, 2^-7, relative
     to the tensor's largest value).  Three calls on the same inputs give the
