@@ -931,8 +931,7 @@ static hipError_t check(int dtype, const AttnArgs& a, bool bwd) {
   if (a.B <= 0 || a.S <= 0 || a.H <= 0 || !a.qkv || !a.o || !a.lse) return hipErrorInvalidValue;
   if (bwd && (!a.dout || !a.dsum || !a.dqkv)) return hipErrorInvalidValue;
   if (a.rope && (!a.rope_tab || a.rope_rows < a.S)) return hipErrorInvalidValue;
-  // bf16: Q and K arrive rotated, or there is no rotation
-  if (a.rope_in_qkv != a.rope || (a.rope && dtype != DT_BF16)) return hipErrorInvalidValue;
+  if (a.rope && dtype != DT_BF16) return hipErrorInvalidValue;
   const int d = a.H * a.dh;
   const bool three_block = a.qkv_hs == a.dh && a.qkv_ko == d && a.qkv_vo == 2 * d;
   const bool per_head = a.qkv_hs == 3 * a.dh && a.qkv_ko == a.dh && a.qkv_vo == 2 * a.dh;

@@ -60,10 +60,9 @@ hipError_t launch_gemm(int dtype, Role role, Epi epi, const GemmArgs& a, hipStre
 // ---------------------------------------------------------------- attention
 struct AttnArgs {
   int B, S, H, dh;
-  int causal, rope;
-  int rope_in_qkv;              // bf16, rope: Q and K in qkv are already rotated (no rotation on
-                                // load); dQ and dK are still rotated back on output
-  float theta;
+  int causal;
+  int rope;                     // bf16 only: Q and K in qkv are rotated; dQ and dK are rotated
+                                // back on output
   const float2* rope_tab;       // rope: (cos, sin) of pos * theta^(-2i/dh), [rope_rows][dh/2]
   int rope_rows;                // positions the table covers (>= S)
   const void* qkv; int ld_qkv;  // [B*S, ld]: Q, K, V of every head
