@@ -153,8 +153,10 @@ __device__ __forceinline__ void heavy_first(int lin, int nq, int nbh, int& rank,
 // per tile, no registers held for the loads), and skips, wave by wave, blocks
 // that the causal mask or the sequence's end leaves empty.  KR 64 and no staging
 // registers keep d_head 128 within two waves per SIMD (one before: nothing
-// overlapped the softmax with MFMAs and LDS reads).  Results leave through LDS as
-// whole rows.
+// overlapped the softmax with MFMAs and LDS reads); only the dK/dV pass still
+// spills there (19 registers causal, 7 not).  Results leave through LDS as whole
+// rows.  The forward's running maximum moves once per 64 keys (128 before), so P is
+// rounded to bf16 at other scales: other bits, the same error against 64 bits.
 // Before -> after, us: 2048 tokens of 512, 32 heads of 128, causal: forward 43 -> 23,
 // dQ 56 -> 40, dK/dV 71 -> 57; 4096 tokens of 256, 16 heads of 64: 15.8 -> 13.6,
 // 20.4 -> 20.4, 28.6 -> 21.4.

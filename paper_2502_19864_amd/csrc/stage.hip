@@ -756,7 +756,7 @@ static ringada_status block_backward(const Ctx& c, int l, const void* G, void* d
     ab.gamma = b.w.norm2_g;
   }
   RG_TRY(run(st, c.s, "adapter_bwd", stop_ffn ? 4.0 * T * d * m : ad_flops,
-             es * ((c.llama ? 3.0 : 5.0) - (stop_ffn ? 1.0 : 0.0)) * T * d,
+             es * ((c.llama ? (ab.dz ? 3.0 : 2.0) : 5.0) - (stop_ffn ? 1.0 : 0.0)) * T * d,
              [&] { return launch_adapter_bwd(c.dt, ab, c.s); }));
   st->dw_pending.push_back(
       AdapterDwArgs{T, d, m, c.S(sb.u2), dz2, c.S(sb.f2), ab.du, b.ad[1].g_up, b.ad[1].g_down, ab.gu});
